@@ -271,9 +271,9 @@ hipError_t launch_packed_path(const ConfigEntry &cfg, int ta, int tb, const Gemm
 {
     __bf16 *ap = reinterpret_cast<__bf16 *>(((uintptr_t)ws + 255) & ~(uintptr_t)255);
     __bf16 *bp = ap + pack_halves(g.m, g.k);
-    hipError_t e = launch_pack(g.A, g.lda, ta != 0, g.m, g.k, g.vec_a, ap, s);
+    hipError_t e = launch_pack(g.A, g.lda, ta != 0, g.m, g.k, ap, s);
     if (e != hipSuccess) return e;
-    e = launch_pack(g.B, g.ldb, tb == 0, g.n, g.k, g.vec_b, bp, s);
+    e = launch_pack(g.B, g.ldb, tb == 0, g.n, g.k, bp, s);
     if (e != hipSuccess) return e;
     PackedArgs p;
     p.g = g;
@@ -285,7 +285,6 @@ hipError_t launch_packed_path(const ConfigEntry &cfg, int ta, int tb, const Gemm
     return cfg.packed(p, group_m, s);
 }
 
-bool aligned16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
 
 int validate(char transa, char transb, int64_t m, int64_t n, int64_t k, float alpha,
              const float *A, int64_t lda, const float *B, int64_t ldb, float *C, int64_t ldc,
@@ -321,9 +320,6 @@ GemmArgs make_args(int64_t m, int64_t n, int64_t k, float alpha, const float *A,
     g.A = A; g.B = B; g.C = C;
     g.lda = lda; g.ldb = ldb; g.ldc = ldc;
     g.alpha = alpha; g.beta = beta;
-    g.vec_a = aligned16(A) && lda % 4 == 0;
-    g.vec_b = aligned16(B) && ldb % 4 == 0;
-    g.vec_c = aligned16(C) && ldc % 4 == 0;
     g.part = nullptr;
     g.tile = 0;
     g.split = 0;
@@ -529,10 +525,10 @@ int build_part(const misgemm_problem *problems, const std::vector<int64_t> &inde
             if (pa.kblocks > 0) {
                 // op(A) is k-contiguous when A is transposed, op(B) when B is not
                 const PackJob ja = {p.A, nullptr, p.lda, p.m, pd.g.k, pa.mp, pack_blocks,
-                                    (pa.mp + 255) / 256, pd.ta != 0, pd.g.vec_a};
+                                    (pa.mp + 255) / 256, pd.ta != 0};
                 pack_blocks += ja.row_blocks * pa.kblocks;
                 const PackJob jb = {p.B, nullptr, p.ldb, p.n, pd.g.k, pa.np, pack_blocks,
-                                    (pa.np + 255) / 256, pd.tb == 0, pd.g.vec_b};
+                                    (pa.np + 255) / 256, pd.tb == 0};
                 pack_blocks += jb.row_blocks * pa.kblocks;
                 jobs.push_back(ja);
                 jobs.push_back(jb);

@@ -15,6 +15,7 @@
 namespace misgemm {
 
 typedef double doublex2 __attribute__((ext_vector_type(2)));
+typedef double doublex2u __attribute__((ext_vector_type(2), aligned(8)));  // at any double address
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------------------
@@ -39,9 +40,12 @@ struct StageF64 {
         else    { r = (c % (R / 2)) * 2;   kk = c / (R / 2); }
     }
 
-    // FAST: whole slice in range, 16-byte aligned.  Otherwise each element
-    // is masked (zero outside the matrix).
-    template <bool FAST>
+    static constexpr int MIN_ROWS = KC ? 1 : 2;  // rows an EDGE load needs
+
+    // MODE: see LoadMode.  EDGE, two rows at one k: the 16-byte load starts
+    // at most at row rows - 2 and store() shifts a chunk that straddles the
+    // last row.
+    template <LoadMode MODE>
     __device__ __forceinline__ void load(const double *X, int64_t ld, int64_t r0, int64_t k0,
                                          int64_t rows, int64_t kdim, int tid)
     {
@@ -51,23 +55,24 @@ struct StageF64 {
             if (CH % NT != 0 && c >= CH) break;
             int r, kk;
             chunk(c, r, kk);
-            const int64_t gr = r0 + r, gk = k0 + kk;
-            if (FAST) {
-                v[s] = *reinterpret_cast<const doublex2 *>(KC ? X + gk + gr * ld
-                                                              : X + gr + gk * ld);
-            } else if (KC) {
-                const bool in = gr < rows;
-                v[s][0] = in && gk < kdim ? X[gk + gr * ld] : 0.0;
-                v[s][1] = in && gk + 1 < kdim ? X[gk + 1 + gr * ld] : 0.0;
+            int64_t gr = r0 + r;
+            const int64_t gk = k0 + kk;
+            if (MODE == MASKED) {
+                const double *p = KC ? X + gk + gr * ld : X + gr + gk * ld;
+#pragma unroll
+                for (int e = 0; e < 2; ++e)
+                    v[s][e] = (KC ? gr < rows && gk + e < kdim : gk < kdim && gr + e < rows)
+                                  ? p[e] : 0.0;
             } else {
-                const bool in = gk < kdim;
-                v[s][0] = in && gr < rows ? X[gr + gk * ld] : 0.0;
-                v[s][1] = in && gr + 1 < rows ? X[gr + 1 + gk * ld] : 0.0;
+                if (MODE == EDGE) gr = min64(gr, rows - MIN_ROWS);
+                v[s] = *reinterpret_cast<const doublex2u *>(KC ? X + gk + gr * ld
+                                                               : X + gr + gk * ld);
             }
         }
     }
 
-    __device__ __forceinline__ void store(double *Xs, int tid) const
+    template <LoadMode MODE>
+    __device__ __forceinline__ void store(double *Xs, int64_t r0, int64_t rows, int tid) const
     {
 #pragma unroll
         for (int s = 0; s < S; ++s) {
@@ -79,7 +84,9 @@ struct StageF64 {
                 Xs[kk * LD + r] = v[s][0];
                 Xs[(kk + 1) * LD + r] = v[s][1];
             } else {
-                *reinterpret_cast<doublex2 *>(Xs + kk * LD + r) = v[s];
+                doublex2 x = v[s];
+                if (MODE == EDGE && r0 + r + 1 == rows) x[0] = x[1];
+                *reinterpret_cast<doublex2 *>(Xs + kk * LD + r) = x;
             }
         }
     }
@@ -92,7 +99,6 @@ struct DArgs {
     double *C;
     int64_t lda, ldb, ldc;
     double alpha, beta;
-    int vec_a, vec_b;  // 16-byte loads legal (aligned base, even ld)
 };
 
 // ---------------------------------------------------------------------------
@@ -141,13 +147,12 @@ struct F64Tile {
 
     __device__ __forceinline__ static void run(const DArgs &g, int64_t m0, int64_t n0, char *smem)
     {
-        const bool fast = m0 + SH::BM <= g.m && n0 + SH::BN <= g.n && g.k % SH::BK == 0 &&
-                          g.vec_a && g.vec_b;
-        if (fast) run_impl<true>(g, m0, n0, smem);
-        else run_impl<false>(g, m0, n0, smem);
+        if (m0 + SH::BM <= g.m && n0 + SH::BN <= g.n) run_impl<INTERIOR>(g, m0, n0, smem);
+        else if (g.m >= SA::MIN_ROWS && g.n >= SB::MIN_ROWS) run_impl<EDGE>(g, m0, n0, smem);
+        else run_impl<MASKED>(g, m0, n0, smem);
     }
 
-    template <bool FAST>
+    template <LoadMode MODE>
     __device__ __forceinline__ static void run_impl(const DArgs &g, int64_t m0, int64_t n0,
                                                     char *smem)
     {
@@ -162,14 +167,12 @@ struct F64Tile {
 #pragma unroll
             for (int j = 0; j < RN; ++j) acc[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
 
-        const int64_t ktiles = (g.k + SH::BK - 1) / SH::BK;
+        const KBlocks<SH::BK> kb(g.k);
+        const int64_t ktiles = kb.count;
         SA sa;
         SB sb;
         if (ktiles > 0) {
-            sa.template load<FAST>(g.A, g.lda, m0, 0, g.m, g.k, tid);
-            sb.template load<FAST>(g.B, g.ldb, n0, 0, g.n, g.k, tid);
-            sa.store(lds, tid);
-            sb.store(lds + SA::ELEMS, tid);
+            load_first<MODE>(sa, sb, g, m0, n0, kb, lds, lds + SA::ELEMS, tid);
         }
         __syncthreads();
         for (int64_t kt = 0; kt < ktiles; ++kt) {
@@ -177,9 +180,9 @@ struct F64Tile {
             double *nxt = lds + ((kt + 1) & 1) * STAGE;
             const bool more = kt + 1 < ktiles;
             if (more) {
-                const int64_t k0 = (kt + 1) * SH::BK;
-                sa.template load<FAST>(g.A, g.lda, m0, k0, g.m, g.k, tid);
-                sb.template load<FAST>(g.B, g.ldb, n0, k0, g.n, g.k, tid);
+                const int64_t k0 = kb.at(kt + 1);
+                sa.template load<MODE>(g.A, g.lda, m0, k0, g.m, g.k, tid);
+                sb.template load<MODE>(g.B, g.ldb, n0, k0, g.n, g.k, tid);
             }
             const double *As = cur + wm * SH::WM + r16;
             const double *Bs = cur + SA::ELEMS + wn * SH::WN + r16;
@@ -199,8 +202,8 @@ struct F64Tile {
                                                                           0, 0, 0);
             }
             if (more) {
-                sa.store(nxt, tid);
-                sb.store(nxt + SA::ELEMS, tid);
+                sa.template store<MODE>(nxt, m0, g.m, tid);
+                sb.template store<MODE>(nxt + SA::ELEMS, n0, g.n, tid);
             }
             __syncthreads();
         }
@@ -245,8 +248,6 @@ hipError_t launch_dgemm_fp64(int ta, int tb, int64_t m, int64_t n, int64_t k, do
     g.A = A; g.B = B; g.C = C;
     g.lda = lda; g.ldb = ldb; g.ldc = ldc;
     g.alpha = alpha; g.beta = beta;
-    g.vec_a = ((uintptr_t)A & 15u) == 0 && lda % 2 == 0;
-    g.vec_b = ((uintptr_t)B & 15u) == 0 && ldb % 2 == 0;
     const int64_t big = ((m + 127) / 128) * ((n + 127) / 128);
     if (big >= cus) return launch_dgemm_shape<DShapeL>(ta, tb, g, s);
     return launch_dgemm_shape<DShapeS>(ta, tb, g, s);

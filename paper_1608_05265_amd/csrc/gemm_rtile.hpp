@@ -46,38 +46,28 @@ struct RShape {
 
 // The N values  op(X)(row, k0 + s), s = 0..N-1 (N = 16 or 8), of one row
 // of op(X) (rows x kdim).  KC: op(X)(r, k) = X[k + r*ld] (k contiguous),
-// else X[r + k*ld].  FAST: row < rows and k0 + N <= kdim hold, and for KC
-// the 16-byte loads are aligned (base 16-byte aligned, ld % 4 == 0; k0 is
-// a multiple of N).  Otherwise entries outside op(X) read as zero and are
-// not loaded.
-template <bool FAST, bool KC, int N>
+// else X[r + k*ld].  MODE: see LoadMode (EDGE: a row past the last is loaded
+// from the last one).
+template <LoadMode MODE, bool KC, int N>
 __device__ __forceinline__ void rload(const float *__restrict__ X, int64_t ld, int64_t row,
                                       int64_t k0, int64_t rows, int64_t kdim, float (&v)[N])
 {
-    if constexpr (KC) {
-        const float *p = X + row * ld + k0;
-        if constexpr (FAST) {
+    if (MODE == EDGE) row = min64(row, rows - 1);
+    const float *p = KC ? X + row * ld + k0 : X + row + k0 * ld;
+    if constexpr (MODE == MASKED) {
+        const bool rok = row < rows;
 #pragma unroll
-            for (int q = 0; q < N / 4; ++q) {
-                const floatx4 t = *reinterpret_cast<const floatx4 *>(p + 4 * q);
+        for (int s = 0; s < N; ++s) v[s] = (rok && k0 + s < kdim) ? p[KC ? s : s * ld] : 0.0f;
+    } else if constexpr (KC) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[4 * q + e] = t[e];
-            }
-        } else {
-            const bool rok = row < rows;
+        for (int q = 0; q < N / 4; ++q) {
+            const floatx4 t = *reinterpret_cast<const floatx4u *>(p + 4 * q);
 #pragma unroll
-            for (int s = 0; s < N; ++s) v[s] = (rok && k0 + s < kdim) ? p[s] : 0.0f;
+            for (int e = 0; e < 4; ++e) v[4 * q + e] = t[e];
         }
     } else {
-        const float *p = X + row + k0 * ld;
-        if constexpr (FAST) {
 #pragma unroll
-            for (int s = 0; s < N; ++s) v[s] = p[s * ld];
-        } else {
-            const bool rok = row < rows;
-#pragma unroll
-            for (int s = 0; s < N; ++s) v[s] = (rok && k0 + s < kdim) ? p[s * ld] : 0.0f;
-        }
+        for (int s = 0; s < N; ++s) v[s] = p[s * ld];
     }
 }
 
@@ -131,13 +121,13 @@ __device__ __forceinline__ void repilogue(const GemmArgs &g, const floatx4 (&acc
             floatx4 out;
 #pragma unroll
             for (int e = 0; e < 4; ++e) out[e] = g.alpha * acc[i][j][e];
-            if (g.vec_c && row + 4 <= g.m) {
+            if (row + 4 <= g.m) {
                 if (use_c0) {
-                    const floatx4 c0 = *reinterpret_cast<const floatx4 *>(p);
+                    const floatx4 c0 = *reinterpret_cast<const floatx4u *>(p);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) out[e] += g.beta * c0[e];
                 }
-                *reinterpret_cast<floatx4 *>(p) = out;
+                *reinterpret_cast<floatx4u *>(p) = out;
             } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
@@ -164,27 +154,24 @@ struct RTileBase {
                                                char *smem)
     {
         static_assert(!SPLIT, "no split-K variant");
-        // op(A) is k-contiguous when transposed, op(B) when not
-        const bool fast = m0 + SH::BM <= g.m && n0 + SH::BN <= g.n && g.k % SH::BK == 0 &&
-                          (!TA || g.vec_a) && (TB || g.vec_b);
-        if (fast) run_impl<true>(g, m0, n0, smem);
-        else run_impl<false>(g, m0, n0, smem);
+        if (m0 + SH::BM <= g.m && n0 + SH::BN <= g.n) run_impl<INTERIOR>(g, m0, n0, smem);
+        else run_impl<EDGE>(g, m0, n0, smem);
     }
 
-    template <bool FAST>
+    template <LoadMode MODE>
     __device__ __forceinline__ static void load(const GemmArgs &g, int64_t m0, int64_t n0,
                                                 int64_t k0, int r, float (&a)[RM][KPL],
                                                 float (&b)[RN][KPL])
     {
 #pragma unroll
         for (int i = 0; i < RM; ++i)
-            rload<FAST, TA, KPL>(g.A, g.lda, m0 + i * 16 + r, k0, g.m, g.k, a[i]);
+            rload<MODE, TA, KPL>(g.A, g.lda, m0 + i * 16 + r, k0, g.m, g.k, a[i]);
 #pragma unroll
         for (int j = 0; j < RN; ++j)
-            rload<FAST, !TB, KPL>(g.B, g.ldb, n0 + j * 16 + r, k0, g.n, g.k, b[j]);
+            rload<MODE, !TB, KPL>(g.B, g.ldb, n0 + j * 16 + r, k0, g.n, g.k, b[j]);
     }
 
-    template <bool FAST>
+    template <LoadMode MODE>
     __device__ __forceinline__ static void run_impl(const GemmArgs &g, int64_t m0, int64_t n0,
                                                     char *smem)
     {
@@ -197,16 +184,26 @@ struct RTileBase {
             for (int j = 0; j < RN; ++j)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.0f;
-        const int64_t chunks = (g.k + SH::BK - 1) / SH::BK;
+        // Full chunks go to the waves in turn; the wave whose turn the ragged
+        // chunk at the end of K would be takes it first, masked, so that the
+        // loop loads full chunks only.
+        const int64_t full = g.k / SH::BK;
         float a[RM][KPL], b[RN][KPL];
-        int64_t c = wave;
-        if (c < chunks) load<FAST>(g, m0, n0, c * SH::BK + KPL * grp, r, a, b);
-        while (c < chunks) {
-            const int64_t cn = c + KW;
+        int64_t next = wave;
+        bool have = true;
+        if (g.k % SH::BK != 0 && full % KW == wave) {
+            load<MASKED>(g, m0, n0, full * SH::BK + KPL * grp, r, a, b);
+        } else {
+            have = next < full;
+            if (have) load<MODE>(g, m0, n0, next * SH::BK + KPL * grp, r, a, b);
+            next += KW;
+        }
+        while (have) {
             float a2[RM][KPL], b2[RN][KPL];
-            if (cn < chunks) load<FAST>(g, m0, n0, cn * SH::BK + KPL * grp, r, a2, b2);
+            have = next < full;
+            if (have) load<MODE>(g, m0, n0, next * SH::BK + KPL * grp, r, a2, b2);
             MATH::template step<RM, RN, KPL>(a, b, acc);
-            if (cn < chunks) {
+            if (have) {
 #pragma unroll
                 for (int i = 0; i < RM; ++i)
 #pragma unroll
@@ -216,7 +213,7 @@ struct RTileBase {
 #pragma unroll
                     for (int s = 0; s < KPL; ++s) b[j][s] = b2[j][s];
             }
-            c = cn;
+            next += KW;
         }
         rwave_sum<KW, RM, RN>(acc, reinterpret_cast<float *>(smem), wave, lane);
         if (wave == 0) repilogue<RM, RN>(g, acc, m0, n0, lane);

@@ -24,6 +24,10 @@
 namespace misgemm {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+// The same four floats in memory at any float address: global memory takes
+// 16-byte accesses at 4-byte alignment, so neither the base nor the leading
+// dimension of a matrix has to be a multiple of 16 bytes.
+typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
@@ -36,7 +40,6 @@ struct GemmArgs {
     float *C;
     int64_t lda, ldb, ldc;
     float alpha, beta;
-    int vec_a, vec_b, vec_c;  // 16-byte vector access legal (aligned base, ld % 4 == 0)
     // Split-K (read only by the split kernels): this workgroup computes the
     // K range of split `split` of `splits` for tile `tile`; its partial sums
     // go to `part`.
@@ -63,20 +66,43 @@ struct Shape {
 // matrix is contiguous along K (KC = true: A transposed, B not transposed)
 // and at X[r + kk*ld] otherwise.
 
-__device__ __forceinline__ floatx4 load4(const float *p, bool vec, bool in_r, int64_t lim_k,
-                                         int64_t step)
-{
-    // Four consecutive elements p[0], p[step], ... masked: element e is read
-    // only when in_r and e < lim_k.  step is 1 for the contiguous direction.
-    floatx4 v;
-    if (vec && in_r && lim_k >= 4) {
-        v = *reinterpret_cast<const floatx4 *>(p);
-    } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = (in_r && e < lim_k) ? p[e * step] : 0.0f;
+// How a K block of an operand is loaded.  A block is MASKED only when it is
+// the ragged end of K (taken first, see k_blocks) or the matrix is smaller
+// than one vector; every other block of every tile is loaded without a mask,
+// so the K loop is straight-line code with 16-byte loads at every size.
+// (Masking each element of every block of a tile as soon as k, a leading
+// dimension or a base was not a multiple of the block or of 16 bytes ran
+// 2047^3 at 70 TFLOP/s and 4095^3 at 83-109, against 104-115 and 133 for the
+// next multiple of 64.)
+enum LoadMode {
+    INTERIOR,  // the whole BM x BN tile is in range
+    EDGE,      // rows past the last are loaded from valid ones: an output row
+               // or column depends on its own row of op(A) or op(B) only, and
+               // those past the end are never stored
+    MASKED     // elements outside the matrix read as zero
+};
+
+// K blocks in the order they are consumed: when k is no multiple of BK the
+// ragged block (the last k % BK of them) comes first, so that it is the
+// prologue's load and the loop has whole blocks only.
+template <int BK>
+struct KBlocks {
+    int64_t count;   // blocks in all
+    int64_t first;   // k offset of block 0
+    int64_t base;    // block b >= 1 starts at base + b * BK
+    bool ragged;     // block 0 is the ragged one
+    __device__ __forceinline__ explicit KBlocks(int64_t k)
+    {
+        const int64_t full = k / BK;
+        ragged = full * BK != k;
+        count = full + (ragged ? 1 : 0);
+        first = ragged ? full * BK : 0;
+        base = ragged ? -BK : 0;
     }
-    return v;
-}
+    __device__ __forceinline__ int64_t at(int64_t b) const { return base + b * BK; }  // b >= 1
+};
+
+__device__ __forceinline__ int64_t min64(int64_t a, int64_t b) { return a < b ? a : b; }
 
 // ---------------------------------------------------------------------------
 // F32 staging: LDS holds X as Xs[kk][r] (r contiguous, row length LD).
@@ -95,15 +121,15 @@ struct StageF32 {
         else    { r = (c % (R / 4)) * 4;   kk = c / (R / 4); }
     }
 
-    static constexpr bool NEEDS_VEC = true;  // the fast path uses 16-byte loads
+    // Rows (of the stored contiguous direction) an EDGE load needs.
+    static constexpr int MIN_ROWS = KC ? 1 : 4;
 
-    // FAST: the caller guarantees the whole R x BK slice is in range and
-    // 16-byte aligned (an interior tile): unmasked loads, no branches, so the
-    // wait counters see straight-line code.  Otherwise every element is
-    // masked (zero fill outside the matrix).
-    template <bool FAST>
+    // MODE: see LoadMode.  EDGE, four rows at one k: the 16-byte load starts
+    // at most at row rows - 4 and store() shifts a chunk that straddles the
+    // last row into place.
+    template <LoadMode MODE>
     __device__ __forceinline__ void load(const float *X, int64_t ld, int64_t r0, int64_t k0,
-                                         int64_t rows, int64_t kdim, bool vec, int tid)
+                                         int64_t rows, int64_t kdim, int tid)
     {
 #pragma unroll
         for (int s = 0; s < S; ++s) {
@@ -111,19 +137,24 @@ struct StageF32 {
             if (CH % NT != 0 && c >= CH) break;
             int r, kk;
             chunk(c, r, kk);
-            const int64_t gr = r0 + r, gk = k0 + kk;
-            if (FAST) {
-                v[s] = *reinterpret_cast<const floatx4 *>(KC ? X + gk + gr * ld : X + gr + gk * ld);
-            } else if (KC) {
-                v[s] = load4(X + gk + gr * ld, vec, gr < rows, kdim - gk, 1);
+            int64_t gr = r0 + r;
+            const int64_t gk = k0 + kk;
+            if (MODE == MASKED) {
+                const float *p = KC ? X + gk + gr * ld : X + gr + gk * ld;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    v[s][e] = (KC ? gr < rows && gk + e < kdim : gk < kdim && gr + e < rows)
+                                  ? p[e] : 0.0f;
             } else {
-                // four consecutive rows at one k: rows are the contiguous direction
-                v[s] = load4(X + gr + gk * ld, vec, gk < kdim, rows - gr, 1);
+                if (MODE == EDGE) gr = min64(gr, rows - MIN_ROWS);
+                v[s] = *reinterpret_cast<const floatx4u *>(KC ? X + gk + gr * ld : X + gr + gk * ld);
             }
         }
     }
 
-    __device__ __forceinline__ void store(float *Xs, int tid) const
+    // r0, rows as in the load of the same MODE.
+    template <LoadMode MODE>
+    __device__ __forceinline__ void store(float *Xs, int64_t r0, int64_t rows, int tid) const
     {
 #pragma unroll
         for (int s = 0; s < S; ++s) {
@@ -131,11 +162,18 @@ struct StageF32 {
             if (CH % NT != 0 && c >= CH) break;
             int r, kk;
             chunk(c, r, kk);
+            floatx4 x = v[s];
             if (KC) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) Xs[(kk + e) * LD + r] = v[s][e];
+                for (int e = 0; e < 4; ++e) Xs[(kk + e) * LD + r] = x[e];
             } else {
-                *reinterpret_cast<floatx4 *>(Xs + kk * LD + r) = v[s];
+                if (MODE == EDGE) {
+                    const int64_t past = r0 + r + 4 - rows;  // 1..3: the load started past rows early
+                    if (past & 1) { x[0] = x[1]; x[1] = x[2]; x[2] = x[3]; }
+                    if (past & 2) { x[0] = x[2]; x[1] = x[3]; }
+                    if (past <= 0) x = v[s];
+                }
+                *reinterpret_cast<floatx4 *>(Xs + kk * LD + r) = x;
             }
         }
     }
@@ -177,46 +215,35 @@ struct StageX3 {
         kk = (c / R) * KS;
     }
 
-    static constexpr bool NEEDS_VEC = KC;  // only the K-contiguous side uses 16-byte loads
+    static constexpr int MIN_ROWS = 1;
 
-    // FAST: the caller guarantees an interior, aligned slice (unmasked loads,
-    // straight-line code); otherwise every element is masked.
-    template <bool FAST>
+    template <LoadMode MODE>
     __device__ __forceinline__ void load(const float *X, int64_t ld, int64_t r0, int64_t k0,
-                                         int64_t rows, int64_t kdim, bool vec, int tid)
+                                         int64_t rows, int64_t kdim, int tid)
     {
-        (void)vec;
 #pragma unroll
         for (int s = 0; s < S; ++s) {
             const int c = tid + s * NT;
             if (!UNITS_FULL && c >= CH) break;
             int r, kk;
             chunk(c, r, kk);
-            const int64_t gr = r0 + r, gk = k0 + kk;
-            if (FAST) {
-                if (KC) {
-                    const float *p = X + gk + gr * ld;
-                    const floatx4 x0 = *reinterpret_cast<const floatx4 *>(p);
-                    const floatx4 x1 = *reinterpret_cast<const floatx4 *>(p + 4);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) { v[s][e] = x0[e]; v[s][4 + e] = x1[e]; }
-                } else {
-                    const float *p = X + gr + gk * ld;
-#pragma unroll
-                    for (int e = 0; e < KS; ++e) v[s][e] = p[e * ld];
-                }
-            } else {
+            int64_t gr = r0 + r;
+            const int64_t gk = k0 + kk;
+            if (MODE == EDGE) gr = min64(gr, rows - 1);
+            const float *p = KC ? X + gk + gr * ld : X + gr + gk * ld;
+            if (MODE == MASKED) {
                 const bool in_r = gr < rows;
-                if (KC) {
-                    const float *p = X + gk + gr * ld;
 #pragma unroll
-                    for (int e = 0; e < KS; ++e) v[s][e] = (in_r && gk + e < kdim) ? p[e] : 0.0f;
-                } else {
-                    const float *p = X + gr + gk * ld;
+                for (int e = 0; e < KS; ++e)
+                    v[s][e] = (in_r && gk + e < kdim) ? p[KC ? e : e * ld] : 0.0f;
+            } else if (KC) {
+                const floatx4 x0 = *reinterpret_cast<const floatx4u *>(p);
+                const floatx4 x1 = *reinterpret_cast<const floatx4u *>(p + 4);
 #pragma unroll
-                    for (int e = 0; e < KS; ++e)
-                        v[s][e] = (in_r && gk + e < kdim) ? p[e * ld] : 0.0f;
-                }
+                for (int e = 0; e < 4; ++e) { v[s][e] = x0[e]; v[s][4 + e] = x1[e]; }
+            } else {
+#pragma unroll
+                for (int e = 0; e < KS; ++e) v[s][e] = p[e * ld];
             }
         }
     }
@@ -248,7 +275,8 @@ struct StageX3 {
         *reinterpret_cast<bf16x8 *>(base + 2 * PART) = p2;
     }
 
-    __device__ __forceinline__ void store(__bf16 *Xs, int tid) const
+    template <LoadMode MODE>
+    __device__ __forceinline__ void store(__bf16 *Xs, int64_t, int64_t, int tid) const
     {
 #pragma unroll
         for (int s = 0; s < S; ++s) {
@@ -278,7 +306,6 @@ __device__ __forceinline__ void epilogue(const GemmArgs &g, const floatx16 (&acc
                                          int64_t row0, int64_t col0, int lane)
 {
     const int half = lane >> 5, l32 = lane & 31;
-    const bool vec = g.vec_c;
     const bool use_c0 = g.beta != 0.0f;
     constexpr int NG = RN * RM * 4;                       // 16-byte groups per lane
     constexpr int GG = EPI_GROUP < NG ? EPI_GROUP : NG;
@@ -293,8 +320,8 @@ __device__ __forceinline__ void epilogue(const GemmArgs &g, const floatx16 (&acc
             const int64_t row = row0 + rm * 32 + gi * 8 + half * 4;
 #pragma unroll
             for (int e = 0; e < 4; ++e) c0[q][e] = 0.0f;
-            if (use_c0 && vec && col < g.n && row + 4 <= g.m)
-                c0[q] = *reinterpret_cast<const floatx4 *>(g.C + col * g.ldc + row);
+            if (use_c0 && col < g.n && row + 4 <= g.m)
+                c0[q] = *reinterpret_cast<const floatx4u *>(g.C + col * g.ldc + row);
         }
 #pragma unroll
         for (int q = 0; q < GG; ++q) {
@@ -306,12 +333,12 @@ __device__ __forceinline__ void epilogue(const GemmArgs &g, const floatx16 (&acc
             floatx4 out;
 #pragma unroll
             for (int e = 0; e < 4; ++e) out[e] = g.alpha * acc[rm][rn][gi * 4 + e];
-            if (vec && row + 4 <= g.m) {
+            if (row + 4 <= g.m) {
                 if (use_c0) {
 #pragma unroll
                     for (int e = 0; e < 4; ++e) out[e] += g.beta * c0[q][e];
                 }
-                *reinterpret_cast<floatx4 *>(p) = out;
+                *reinterpret_cast<floatx4u *>(p) = out;
             } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
@@ -366,6 +393,25 @@ __device__ __forceinline__ void finish(const GemmArgs &g, const floatx16 (&acc)[
     }
 }
 
+// The first K block of a tile into LDS (masked when it is the ragged one).
+template <LoadMode MODE, class SA, class SB, class ARGS, int BK, class T>
+__device__ __forceinline__ void load_first(SA &sa, SB &sb, const ARGS &g, int64_t m0,
+                                           int64_t n0, const KBlocks<BK> &kb, T *as, T *bs,
+                                           int tid)
+{
+    if (MODE != MASKED && kb.ragged) {
+        sa.template load<MASKED>(g.A, g.lda, m0, kb.first, g.m, g.k, tid);
+        sb.template load<MASKED>(g.B, g.ldb, n0, kb.first, g.n, g.k, tid);
+        sa.template store<MASKED>(as, m0, g.m, tid);
+        sb.template store<MASKED>(bs, n0, g.n, tid);
+    } else {
+        sa.template load<MODE>(g.A, g.lda, m0, kb.first, g.m, g.k, tid);
+        sb.template load<MODE>(g.B, g.ldb, n0, kb.first, g.n, g.k, tid);
+        sa.template store<MODE>(as, m0, g.m, tid);
+        sb.template store<MODE>(bs, n0, g.n, tid);
+    }
+}
+
 // ---------------------------------------------------------------------------
 // The tile body: stage -> multiply -> epilogue for tile (m0, n0).
 // ---------------------------------------------------------------------------
@@ -377,19 +423,16 @@ struct F32Tile {
     static constexpr int LDS_BYTES = 2 * STAGE_FLOATS * 4;
     static constexpr int NT = SH::NT;
 
-    // Interior tiles whose K range is a whole number of blocks take the
-    // unmasked load path; every other tile masks its loads.
     template <bool SPLIT = false>
     __device__ __forceinline__ static void run(const GemmArgs &g, int64_t m0, int64_t n0,
                                                char *smem)
     {
-        const bool fast = m0 + SH::BM <= g.m && n0 + SH::BN <= g.n && g.k % SH::BK == 0 &&
-                          (g.vec_a || !SA::NEEDS_VEC) && (g.vec_b || !SB::NEEDS_VEC);
-        if (fast) run_impl<true, SPLIT>(g, m0, n0, smem);
-        else run_impl<false, SPLIT>(g, m0, n0, smem);
+        if (m0 + SH::BM <= g.m && n0 + SH::BN <= g.n) run_impl<INTERIOR, SPLIT>(g, m0, n0, smem);
+        else if (g.m >= SA::MIN_ROWS && g.n >= SB::MIN_ROWS) run_impl<EDGE, SPLIT>(g, m0, n0, smem);
+        else run_impl<MASKED, SPLIT>(g, m0, n0, smem);
     }
 
-    template <bool FAST, bool SPLIT>
+    template <LoadMode MODE, bool SPLIT>
     __device__ __forceinline__ static void run_impl(const GemmArgs &g, int64_t m0, int64_t n0,
                                                     char *smem)
     {
@@ -406,7 +449,8 @@ struct F32Tile {
 #pragma unroll
                 for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
 
-        const int64_t ktiles = (g.k + SH::BK - 1) / SH::BK;
+        const KBlocks<SH::BK> kb(g.k);
+        const int64_t ktiles = kb.count;
         SA sa;
         SB sb;
         // PF2: a second register set takes the global loads of block kt+2
@@ -415,14 +459,11 @@ struct F32Tile {
         SA sa2;
         SB sb2;
         if (ktiles > 0) {
-            sa.template load<FAST>(g.A, g.lda, m0, 0, g.m, g.k, g.vec_a, tid);
-            sb.template load<FAST>(g.B, g.ldb, n0, 0, g.n, g.k, g.vec_b, tid);
-            sa.store(lds, tid);
-            sb.store(lds + SA::FLOATS, tid);
+            load_first<MODE>(sa, sb, g, m0, n0, kb, lds, lds + SA::FLOATS, tid);
         }
         if (PF2 && ktiles > 1) {
-            sa.template load<FAST>(g.A, g.lda, m0, SH::BK, g.m, g.k, g.vec_a, tid);
-            sb.template load<FAST>(g.B, g.ldb, n0, SH::BK, g.n, g.k, g.vec_b, tid);
+            sa.template load<MODE>(g.A, g.lda, m0, kb.at(1), g.m, g.k, tid);
+            sb.template load<MODE>(g.B, g.ldb, n0, kb.at(1), g.n, g.k, tid);
         }
         __syncthreads();
         for (int64_t kt = 0; kt < ktiles; ++kt) {
@@ -431,14 +472,14 @@ struct F32Tile {
             const bool more = kt + 1 < ktiles;
             if (PF2) {
                 if (kt + 2 < ktiles) {
-                    const int64_t k0 = (kt + 2) * SH::BK;
-                    sa2.template load<FAST>(g.A, g.lda, m0, k0, g.m, g.k, g.vec_a, tid);
-                    sb2.template load<FAST>(g.B, g.ldb, n0, k0, g.n, g.k, g.vec_b, tid);
+                    const int64_t k0 = kb.at(kt + 2);
+                    sa2.template load<MODE>(g.A, g.lda, m0, k0, g.m, g.k, tid);
+                    sb2.template load<MODE>(g.B, g.ldb, n0, k0, g.n, g.k, tid);
                 }
             } else if (more) {
-                const int64_t k0 = (kt + 1) * SH::BK;
-                sa.template load<FAST>(g.A, g.lda, m0, k0, g.m, g.k, g.vec_a, tid);
-                sb.template load<FAST>(g.B, g.ldb, n0, k0, g.n, g.k, g.vec_b, tid);
+                const int64_t k0 = kb.at(kt + 1);
+                sa.template load<MODE>(g.A, g.lda, m0, k0, g.m, g.k, tid);
+                sb.template load<MODE>(g.B, g.ldb, n0, k0, g.n, g.k, tid);
             }
             const float *As = cur + wm * SH::WM + l32;
             const float *Bs = cur + SA::FLOATS + wn * SH::WN + l32;
@@ -458,8 +499,8 @@ struct F32Tile {
                                                                           0, 0, 0);
             }
             if (more) {
-                sa.store(nxt, tid);
-                sb.store(nxt + SA::FLOATS, tid);
+                sa.template store<MODE>(nxt, m0, g.m, tid);
+                sb.template store<MODE>(nxt + SA::FLOATS, n0, g.n, tid);
             }
             if (PF2 && kt + 2 < ktiles) {
                 sa = sa2;
@@ -500,7 +541,9 @@ struct F32PTile {
         for (int j = 0; j < RN; ++j) b[j] = Bs[kr * SB::LD + j * 32];
     }
 
-    __device__ __forceinline__ static void body(floatx16 (&acc)[RM][RN], const float *cur,
+    template <LoadMode MODE>
+    __device__ __forceinline__ static void body(floatx16 (&acc)[RM][RN], const GemmArgs &g,
+                                                int64_t m0, int64_t n0, const float *cur,
                                                 float *nxt, const SA &sa, const SB &sb, int tid,
                                                 int wm, int wn, int half, int l32)
     {
@@ -522,27 +565,24 @@ struct F32PTile {
                                                                       acc[i][j], 0, 0, 0);
                     if (ks == STORE_STEP && i == 0 && j == 0) {
                         __builtin_amdgcn_sched_barrier(0);
-                        sa.store(nxt, tid);
-                        sb.store(nxt + SA::FLOATS, tid);
+                        sa.template store<MODE>(nxt, m0, g.m, tid);
+                        sb.template store<MODE>(nxt + SA::FLOATS, n0, g.n, tid);
                         __builtin_amdgcn_sched_barrier(0);
                     }
                 }
         }
     }
 
-    // Interior tiles whose K range is a whole number of blocks take the
-    // unmasked load path; every other tile masks its loads.
     template <bool SPLIT = false>
     __device__ __forceinline__ static void run(const GemmArgs &g, int64_t m0, int64_t n0,
                                                char *smem)
     {
-        const bool fast = m0 + SH::BM <= g.m && n0 + SH::BN <= g.n && g.k % SH::BK == 0 &&
-                          (g.vec_a || !SA::NEEDS_VEC) && (g.vec_b || !SB::NEEDS_VEC);
-        if (fast) run_impl<true, SPLIT>(g, m0, n0, smem);
-        else run_impl<false, SPLIT>(g, m0, n0, smem);
+        if (m0 + SH::BM <= g.m && n0 + SH::BN <= g.n) run_impl<INTERIOR, SPLIT>(g, m0, n0, smem);
+        else if (g.m >= SA::MIN_ROWS && g.n >= SB::MIN_ROWS) run_impl<EDGE, SPLIT>(g, m0, n0, smem);
+        else run_impl<MASKED, SPLIT>(g, m0, n0, smem);
     }
 
-    template <bool FAST, bool SPLIT>
+    template <LoadMode MODE, bool SPLIT>
     __device__ __forceinline__ static void run_impl(const GemmArgs &g, int64_t m0, int64_t n0,
                                                     char *smem)
     {
@@ -559,27 +599,25 @@ struct F32PTile {
 #pragma unroll
                 for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
 
-        const int64_t ktiles = (g.k + SH::BK - 1) / SH::BK;
+        const KBlocks<SH::BK> kb(g.k);
+        const int64_t ktiles = kb.count;
         SA sa;
         SB sb;
         if (ktiles > 0) {
-            sa.template load<FAST>(g.A, g.lda, m0, 0, g.m, g.k, g.vec_a, tid);
-            sb.template load<FAST>(g.B, g.ldb, n0, 0, g.n, g.k, g.vec_b, tid);
-            sa.store(lds, tid);
-            sb.store(lds + SA::FLOATS, tid);
+            load_first<MODE>(sa, sb, g, m0, n0, kb, lds, lds + SA::FLOATS, tid);
         }
         __syncthreads();
         for (int64_t kt = 0; kt < ktiles; ++kt) {
             const float *cur = lds + (kt & 1) * STAGE_FLOATS;
             float *nxt = lds + ((kt + 1) & 1) * STAGE_FLOATS;
             if (kt + 1 < ktiles) {
-                const int64_t k0 = (kt + 1) * SH::BK;
-                sa.template load<FAST>(g.A, g.lda, m0, k0, g.m, g.k, g.vec_a, tid);
-                sb.template load<FAST>(g.B, g.ldb, n0, k0, g.n, g.k, g.vec_b, tid);
+                const int64_t k0 = kb.at(kt + 1);
+                sa.template load<MODE>(g.A, g.lda, m0, k0, g.m, g.k, tid);
+                sb.template load<MODE>(g.B, g.ldb, n0, k0, g.n, g.k, tid);
             }
             // On the last block the store rewrites the idle buffer with data
             // already consumed; nothing reads it afterwards.
-            body(acc, cur, nxt, sa, sb, tid, wm, wn, half, l32);
+            body<MODE>(acc, g, m0, n0, cur, nxt, sa, sb, tid, wm, wn, half, l32);
             __syncthreads();
         }
         finish<SPLIT, RM, RN>(g, acc, m0 + wm * SH::WM, n0 + wn * SH::WN, tid, NT);
@@ -595,19 +633,16 @@ struct X3Tile {
     static constexpr int LDS_BYTES = 2 * STAGE_HALVES * 2;
     static constexpr int NT = SH::NT;
 
-    // Interior tiles whose K range is a whole number of blocks take the
-    // unmasked load path; every other tile masks its loads.
     template <bool SPLIT = false>
     __device__ __forceinline__ static void run(const GemmArgs &g, int64_t m0, int64_t n0,
                                                char *smem)
     {
-        const bool fast = m0 + SH::BM <= g.m && n0 + SH::BN <= g.n && g.k % SH::BK == 0 &&
-                          (g.vec_a || !SA::NEEDS_VEC) && (g.vec_b || !SB::NEEDS_VEC);
-        if (fast) run_impl<true, SPLIT>(g, m0, n0, smem);
-        else run_impl<false, SPLIT>(g, m0, n0, smem);
+        if (m0 + SH::BM <= g.m && n0 + SH::BN <= g.n) run_impl<INTERIOR, SPLIT>(g, m0, n0, smem);
+        else if (g.m >= SA::MIN_ROWS && g.n >= SB::MIN_ROWS) run_impl<EDGE, SPLIT>(g, m0, n0, smem);
+        else run_impl<MASKED, SPLIT>(g, m0, n0, smem);
     }
 
-    template <bool FAST, bool SPLIT>
+    template <LoadMode MODE, bool SPLIT>
     __device__ __forceinline__ static void run_impl(const GemmArgs &g, int64_t m0, int64_t n0,
                                                     char *smem)
     {
@@ -633,14 +668,12 @@ struct X3Tile {
                     for (int e = 0; e < 16; ++e) lo[i][j][e] = 0.0f;
         }
 
-        const int64_t ktiles = (g.k + SH::BK - 1) / SH::BK;
+        const KBlocks<SH::BK> kb(g.k);
+        const int64_t ktiles = kb.count;
         SA sa;
         SB sb;
         if (ktiles > 0) {
-            sa.template load<FAST>(g.A, g.lda, m0, 0, g.m, g.k, g.vec_a, tid);
-            sb.template load<FAST>(g.B, g.ldb, n0, 0, g.n, g.k, g.vec_b, tid);
-            sa.store(lds, tid);
-            sb.store(lds + SA::HALVES, tid);
+            load_first<MODE>(sa, sb, g, m0, n0, kb, lds, lds + SA::HALVES, tid);
         }
         __syncthreads();
         for (int64_t kt = 0; kt < ktiles; ++kt) {
@@ -648,9 +681,9 @@ struct X3Tile {
             __bf16 *nxt = lds + ((kt + 1) & 1) * STAGE_HALVES;
             const bool more = kt + 1 < ktiles;
             if (more) {
-                const int64_t k0 = (kt + 1) * SH::BK;
-                sa.template load<FAST>(g.A, g.lda, m0, k0, g.m, g.k, g.vec_a, tid);
-                sb.template load<FAST>(g.B, g.ldb, n0, k0, g.n, g.k, g.vec_b, tid);
+                const int64_t k0 = kb.at(kt + 1);
+                sa.template load<MODE>(g.A, g.lda, m0, k0, g.m, g.k, tid);
+                sb.template load<MODE>(g.B, g.ldb, n0, k0, g.n, g.k, tid);
             }
             const __bf16 *As = cur + (wm * SH::WM + l32) * SA::LD + half * 8;
             const __bf16 *Bs = cur + SA::HALVES + (wn * SH::WN + l32) * SB::LD + half * 8;
@@ -684,8 +717,8 @@ struct X3Tile {
                     }
             }
             if (more) {
-                sa.store(nxt, tid);
-                sb.store(nxt + SA::HALVES, tid);
+                sa.template store<MODE>(nxt, m0, g.m, tid);
+                sb.template store<MODE>(nxt + SA::HALVES, n0, g.n, tid);
             }
             __syncthreads();
         }
@@ -854,19 +887,16 @@ struct X3PTile {
         }
     }
 
-    // Interior tiles whose K range is a whole number of blocks take the
-    // unmasked load path; every other tile masks its loads.
     template <bool SPLIT = false>
     __device__ __forceinline__ static void run(const GemmArgs &g, int64_t m0, int64_t n0,
                                                char *smem)
     {
-        const bool fast = m0 + SH::BM <= g.m && n0 + SH::BN <= g.n && g.k % SH::BK == 0 &&
-                          (g.vec_a || !SA::NEEDS_VEC) && (g.vec_b || !SB::NEEDS_VEC);
-        if (fast) run_impl<true, SPLIT>(g, m0, n0, smem);
-        else run_impl<false, SPLIT>(g, m0, n0, smem);
+        if (m0 + SH::BM <= g.m && n0 + SH::BN <= g.n) run_impl<INTERIOR, SPLIT>(g, m0, n0, smem);
+        else if (g.m >= SA::MIN_ROWS && g.n >= SB::MIN_ROWS) run_impl<EDGE, SPLIT>(g, m0, n0, smem);
+        else run_impl<MASKED, SPLIT>(g, m0, n0, smem);
     }
 
-    template <bool FAST, bool SPLIT>
+    template <LoadMode MODE, bool SPLIT>
     __device__ __forceinline__ static void run_impl(const GemmArgs &g, int64_t m0, int64_t n0,
                                                     char *smem)
     {
@@ -883,7 +913,8 @@ struct X3PTile {
 #pragma unroll
                 for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
 
-        const int64_t ktiles = (g.k + SH::BK - 1) / SH::BK;
+        const KBlocks<SH::BK> kb(g.k);
+        const int64_t ktiles = kb.count;
         if constexpr (PF2) {
             // Two register sets: the global loads of block kt+2 go to the
             // second set at the top of block kt, while the first set (block
@@ -895,23 +926,20 @@ struct X3PTile {
             SA sa, sa2;
             SB sb, sb2;
             if (ktiles > 0) {
-                sa.template load<FAST>(g.A, g.lda, m0, 0, g.m, g.k, g.vec_a, tid);
-                sb.template load<FAST>(g.B, g.ldb, n0, 0, g.n, g.k, g.vec_b, tid);
-                sa.store(lds, tid);
-                sb.store(lds + SA::HALVES, tid);
+                load_first<MODE>(sa, sb, g, m0, n0, kb, lds, lds + SA::HALVES, tid);
             }
             if (ktiles > 1) {
-                sa.template load<FAST>(g.A, g.lda, m0, SH::BK, g.m, g.k, g.vec_a, tid);
-                sb.template load<FAST>(g.B, g.ldb, n0, SH::BK, g.n, g.k, g.vec_b, tid);
+                sa.template load<MODE>(g.A, g.lda, m0, kb.at(1), g.m, g.k, tid);
+                sb.template load<MODE>(g.B, g.ldb, n0, kb.at(1), g.n, g.k, tid);
             }
             __syncthreads();
             for (int64_t kt = 0; kt < ktiles; ++kt) {
                 const __bf16 *cur = lds + (kt & 1) * STAGE_HALVES;
                 __bf16 *nxt = lds + ((kt + 1) & 1) * STAGE_HALVES;
                 if (kt + 2 < ktiles) {
-                    const int64_t k0 = (kt + 2) * SH::BK;
-                    sa2.template load<FAST>(g.A, g.lda, m0, k0, g.m, g.k, g.vec_a, tid);
-                    sb2.template load<FAST>(g.B, g.ldb, n0, k0, g.n, g.k, g.vec_b, tid);
+                    const int64_t k0 = kb.at(kt + 2);
+                    sa2.template load<MODE>(g.A, g.lda, m0, k0, g.m, g.k, tid);
+                    sb2.template load<MODE>(g.B, g.ldb, n0, k0, g.n, g.k, tid);
                 }
                 // a store whose block does not exist rewrites an idle stage
                 // that nothing reads again
@@ -928,19 +956,16 @@ struct X3PTile {
         SA sa;
         SB sb;
         if (ktiles > 0) {
-            sa.template load<FAST>(g.A, g.lda, m0, 0, g.m, g.k, g.vec_a, tid);
-            sb.template load<FAST>(g.B, g.ldb, n0, 0, g.n, g.k, g.vec_b, tid);
-            sa.store(lds, tid);
-            sb.store(lds + SA::HALVES, tid);
+            load_first<MODE>(sa, sb, g, m0, n0, kb, lds, lds + SA::HALVES, tid);
         }
         __syncthreads();
         for (int64_t kt = 0; kt < ktiles; ++kt) {
             const __bf16 *cur = lds + (kt & 1) * STAGE_HALVES;
             __bf16 *nxt = lds + ((kt + 1) & 1) * STAGE_HALVES;
             if (kt + 1 < ktiles) {
-                const int64_t k0 = (kt + 1) * SH::BK;
-                sa.template load<FAST>(g.A, g.lda, m0, k0, g.m, g.k, g.vec_a, tid);
-                sb.template load<FAST>(g.B, g.ldb, n0, k0, g.n, g.k, g.vec_b, tid);
+                const int64_t k0 = kb.at(kt + 1);
+                sa.template load<MODE>(g.A, g.lda, m0, k0, g.m, g.k, tid);
+                sb.template load<MODE>(g.B, g.ldb, n0, k0, g.n, g.k, tid);
             }
             // On the last block the store rewrites the idle buffer with the
             // block already consumed; nothing reads it afterwards.  One body
@@ -1019,13 +1044,12 @@ struct F32WTile {
                                                char *smem)
     {
         static_assert(!SPLIT, "no split-K variant");
-        const bool fast = m0 + SH::BM <= g.m && n0 + SH::BN <= g.n && g.k % SH::BK == 0 &&
-                          (g.vec_a || !SA::NEEDS_VEC) && (g.vec_b || !SB::NEEDS_VEC);
-        if (fast) run_impl<true>(g, m0, n0, smem);
-        else run_impl<false>(g, m0, n0, smem);
+        if (m0 + SH::BM <= g.m && n0 + SH::BN <= g.n) run_impl<INTERIOR>(g, m0, n0, smem);
+        else if (g.m >= SA::MIN_ROWS && g.n >= SB::MIN_ROWS) run_impl<EDGE>(g, m0, n0, smem);
+        else run_impl<MASKED>(g, m0, n0, smem);
     }
 
-    template <bool FAST>
+    template <LoadMode MODE>
     __device__ __forceinline__ static void run_impl(const GemmArgs &g, int64_t m0, int64_t n0,
                                                     char *smem)
     {
@@ -1039,14 +1063,12 @@ struct F32WTile {
             for (int j = 0; j < RN; ++j)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
-        const int64_t ktiles = (g.k + SH::BK - 1) / SH::BK;
+        const KBlocks<SH::BK> kb(g.k);
+        const int64_t ktiles = kb.count;
         SA sa;
         SB sb;
         if (ktiles > 0) {
-            sa.template load<FAST>(g.A, g.lda, m0, 0, g.m, g.k, g.vec_a, tid);
-            sb.template load<FAST>(g.B, g.ldb, n0, 0, g.n, g.k, g.vec_b, tid);
-            sa.store(lds, tid);
-            sb.store(lds + SA::FLOATS, tid);
+            load_first<MODE>(sa, sb, g, m0, n0, kb, lds, lds + SA::FLOATS, tid);
         }
         __syncthreads();
         for (int64_t kt = 0; kt < ktiles; ++kt) {
@@ -1054,9 +1076,9 @@ struct F32WTile {
             float *nxt = lds + ((kt + 1) & 1) * STAGE_FLOATS;
             const bool more = kt + 1 < ktiles;
             if (more) {
-                const int64_t k0 = (kt + 1) * SH::BK;
-                sa.template load<FAST>(g.A, g.lda, m0, k0, g.m, g.k, g.vec_a, tid);
-                sb.template load<FAST>(g.B, g.ldb, n0, k0, g.n, g.k, g.vec_b, tid);
+                const int64_t k0 = kb.at(kt + 1);
+                sa.template load<MODE>(g.A, g.lda, m0, k0, g.m, g.k, tid);
+                sb.template load<MODE>(g.B, g.ldb, n0, k0, g.n, g.k, tid);
             }
             const float *As = cur + l32;
             const float *Bs = cur + SA::FLOATS + l32;
@@ -1076,8 +1098,8 @@ struct F32WTile {
                                                                           0, 0, 0);
             }
             if (more) {
-                sa.store(nxt, tid);
-                sb.store(nxt + SA::FLOATS, tid);
+                sa.template store<MODE>(nxt, m0, g.m, tid);
+                sb.template store<MODE>(nxt + SA::FLOATS, n0, g.n, tid);
             }
             __syncthreads();
         }
@@ -1106,13 +1128,12 @@ struct X3WTile {
                                                char *smem)
     {
         static_assert(!SPLIT, "no split-K variant");
-        const bool fast = m0 + SH::BM <= g.m && n0 + SH::BN <= g.n && g.k % SH::BK == 0 &&
-                          (g.vec_a || !SA::NEEDS_VEC) && (g.vec_b || !SB::NEEDS_VEC);
-        if (fast) run_impl<true>(g, m0, n0, smem);
-        else run_impl<false>(g, m0, n0, smem);
+        if (m0 + SH::BM <= g.m && n0 + SH::BN <= g.n) run_impl<INTERIOR>(g, m0, n0, smem);
+        else if (g.m >= SA::MIN_ROWS && g.n >= SB::MIN_ROWS) run_impl<EDGE>(g, m0, n0, smem);
+        else run_impl<MASKED>(g, m0, n0, smem);
     }
 
-    template <bool FAST>
+    template <LoadMode MODE>
     __device__ __forceinline__ static void run_impl(const GemmArgs &g, int64_t m0, int64_t n0,
                                                     char *smem)
     {
@@ -1126,14 +1147,12 @@ struct X3WTile {
             for (int j = 0; j < RN; ++j)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
-        const int64_t ktiles = (g.k + SH::BK - 1) / SH::BK;
+        const KBlocks<SH::BK> kb(g.k);
+        const int64_t ktiles = kb.count;
         SA sa;
         SB sb;
         if (ktiles > 0) {
-            sa.template load<FAST>(g.A, g.lda, m0, 0, g.m, g.k, g.vec_a, tid);
-            sb.template load<FAST>(g.B, g.ldb, n0, 0, g.n, g.k, g.vec_b, tid);
-            sa.store(lds, tid);
-            sb.store(lds + SA::HALVES, tid);
+            load_first<MODE>(sa, sb, g, m0, n0, kb, lds, lds + SA::HALVES, tid);
         }
         __syncthreads();
         for (int64_t kt = 0; kt < ktiles; ++kt) {
@@ -1141,9 +1160,9 @@ struct X3WTile {
             __bf16 *nxt = lds + ((kt + 1) & 1) * STAGE_HALVES;
             const bool more = kt + 1 < ktiles;
             if (more) {
-                const int64_t k0 = (kt + 1) * SH::BK;
-                sa.template load<FAST>(g.A, g.lda, m0, k0, g.m, g.k, g.vec_a, tid);
-                sb.template load<FAST>(g.B, g.ldb, n0, k0, g.n, g.k, g.vec_b, tid);
+                const int64_t k0 = kb.at(kt + 1);
+                sa.template load<MODE>(g.A, g.lda, m0, k0, g.m, g.k, tid);
+                sb.template load<MODE>(g.B, g.ldb, n0, k0, g.n, g.k, tid);
             }
             const __bf16 *As = cur + l32 * SA::LD + half * 8;
             const __bf16 *Bs = cur + SA::HALVES + l32 * SB::LD + half * 8;
@@ -1177,8 +1196,8 @@ struct X3WTile {
                     }
             }
             if (more) {
-                sa.store(nxt, tid);
-                sb.store(nxt + SA::HALVES, tid);
+                sa.template store<MODE>(nxt, m0, g.m, tid);
+                sb.template store<MODE>(nxt + SA::HALVES, n0, g.n, tid);
             }
             __syncthreads();
         }

@@ -43,7 +43,7 @@ __host__ __device__ inline int64_t pack_halves(int64_t rows, int64_t k)
 // written as zeros.
 template <bool KC>
 __device__ __forceinline__ void pack_unit(const float *__restrict__ X, int64_t ld, int64_t rows,
-                                          int64_t kdim, int64_t rows_pad, int vec,
+                                          int64_t kdim, int64_t rows_pad,
                                           __bf16 *__restrict__ out, int64_t r, int64_t kb)
 {
     const int64_t k0 = kb * PACK_K;
@@ -51,10 +51,10 @@ __device__ __forceinline__ void pack_unit(const float *__restrict__ X, int64_t l
     const bool in_r = r < rows;
     if (KC) {
         const float *p = X + k0 + r * ld;
-        if (vec && in_r && k0 + PACK_K <= kdim) {
+        if (in_r && k0 + PACK_K <= kdim) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const floatx4 x = *reinterpret_cast<const floatx4 *>(p + 4 * q);
+                const floatx4 x = *reinterpret_cast<const floatx4u *>(p + 4 * q);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) v[4 * q + e] = x[e];
             }
@@ -87,10 +87,10 @@ __device__ __forceinline__ void pack_unit(const float *__restrict__ X, int64_t l
 template <bool KC>
 __global__ __launch_bounds__(256) void pack_x3_kernel(const float *__restrict__ X, int64_t ld,
                                                       int64_t rows, int64_t kdim,
-                                                      int64_t rows_pad, int vec,
+                                                      int64_t rows_pad,
                                                       __bf16 *__restrict__ out)
 {
-    pack_unit<KC>(X, ld, rows, kdim, rows_pad, vec, out, (int64_t)blockIdx.x * 256 + threadIdx.x,
+    pack_unit<KC>(X, ld, rows, kdim, rows_pad, out, (int64_t)blockIdx.x * 256 + threadIdx.x,
                   blockIdx.y);
 }
 
@@ -102,12 +102,12 @@ struct PackJob {
     __bf16 *out;
     int64_t ld, rows, kdim, rows_pad;
     int64_t first_block, row_blocks;
-    int32_t kc, vec;
+    int32_t kc;
 };
 
 // Arguments of the packed tile kernel.
 struct PackedArgs {
-    GemmArgs g;           // m, n, C, ldc, alpha, beta, vec_c (A, B, k unused)
+    GemmArgs g;           // m, n, C, ldc, alpha, beta (A, B, k unused)
     const __bf16 *Ap;     // packed op(A): rows m
     const __bf16 *Bp;     // packed op(B): rows n
     int64_t mp, np;       // padded row counts

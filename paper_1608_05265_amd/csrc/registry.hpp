@@ -223,7 +223,7 @@ void register_x3(std::vector<ConfigEntry> &out);
 void register_x3k(std::vector<ConfigEntry> &out);
 
 // Pack op(X) (rows x k, KC: k contiguous) into split panels (packed_x3.hpp).
-hipError_t launch_pack(const float *X, int64_t ld, bool kc, int64_t rows, int64_t k, int vec,
+hipError_t launch_pack(const float *X, int64_t ld, bool kc, int64_t rows, int64_t k,
                        __bf16 *out, hipStream_t s);
 // Pack every operand of a batch in one launch: jobs sorted by first_block,
 // `blocks` = the blocks of all jobs.

@@ -49,17 +49,17 @@ hipError_t launch_packed_direct(const PackedArgs &p, int group_m, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_pack(const float *X, int64_t ld, bool kc, int64_t rows, int64_t k, int vec,
+hipError_t launch_pack(const float *X, int64_t ld, bool kc, int64_t rows, int64_t k,
                        __bf16 *out, hipStream_t s)
 {
     const int64_t rp = pack_rows_pad(rows), kb = pack_kblocks(k);
     const dim3 grid((unsigned)(rp / 256), (unsigned)kb);
     if (kc)
-        hipLaunchKernelGGL((pack_x3_kernel<true>), grid, dim3(256), 0, s, X, ld, rows, k, rp, vec,
+        hipLaunchKernelGGL((pack_x3_kernel<true>), grid, dim3(256), 0, s, X, ld, rows, k, rp,
                            out);
     else
         hipLaunchKernelGGL((pack_x3_kernel<false>), grid, dim3(256), 0, s, X, ld, rows, k, rp,
-                           vec, out);
+                           out);
     return hipGetLastError();
 }
 
@@ -80,8 +80,8 @@ __global__ __launch_bounds__(256) void pack_batch_kernel(const PackJob *__restri
     const int64_t r = (local % j.row_blocks) * 256 + threadIdx.x;
     const int64_t kb = local / j.row_blocks;
     if (r >= j.rows_pad) return;
-    if (j.kc) pack_unit<true>(j.X, j.ld, j.rows, j.kdim, j.rows_pad, j.vec, j.out, r, kb);
-    else pack_unit<false>(j.X, j.ld, j.rows, j.kdim, j.rows_pad, j.vec, j.out, r, kb);
+    if (j.kc) pack_unit<true>(j.X, j.ld, j.rows, j.kdim, j.rows_pad, j.out, r, kb);
+    else pack_unit<false>(j.X, j.ld, j.rows, j.kdim, j.rows_pad, j.out, r, kb);
 }
 
 hipError_t launch_pack_batch(const PackJob *jobs, int njobs, int64_t blocks, hipStream_t s)
