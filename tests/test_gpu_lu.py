@@ -334,3 +334,60 @@ def test_lu_at_the_papers_size():
         r = oracle.hpl_scaled_residual(a, x, b, EPS32)
         assert r < 16.0, "mode %d: scaled residual %.3f" % (mode, r)
         print("N=4608 mode %d: HPL scaled residual %.4f (eps 2^-24)" % (mode, r))
+
+
+def _factor_waiting(a, polls):
+    """The factorization whose panels' first workgroup waits `polls` polls for
+    the others (negative: not at all)."""
+    import ctypes
+
+    import torch
+    import paper_1608_05265_amd as mg
+    n = a.shape[0]
+    fn = mg._load().misgemm_sgetrf_waiting
+    fn.argtypes = [ctypes.c_int64, ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p,
+                   ctypes.c_void_p, ctypes.c_int, ctypes.c_int, ctypes.c_void_p]
+    A = torch.from_numpy(np.ascontiguousarray(a.T)).to("cuda:0")
+    ipiv = torch.empty(n, dtype=torch.int64, device="cuda:0")
+    info = torch.empty(1, dtype=torch.int32, device="cuda:0")
+    rc = fn(n, A.data_ptr(), n, ipiv.data_ptr(), info.data_ptr(), 0, polls,
+            torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert rc == 0
+    return A.cpu().numpy().T, ipiv.cpu().numpy(), int(info.item())
+
+
+@pytest.mark.parametrize("n", [1025, 2500])
+def test_lu_panel_workgroups_that_do_not_meet(n):
+    """A panel whose workgroups do not all arrive in time is factored by the
+    first one alone: the same pivots as the oracle's where they are unique,
+    factors to FP32 accuracy."""
+    rng = np.random.default_rng(51)
+    d = rng.uniform(-1, 1, (n, n)) + np.diag(rng.uniform(n, 2 * n, n))
+    a = d[rng.permutation(n)].astype(np.float32)
+    lu, ipiv, info = _factor_waiting(a, -1)
+    lu_o, ipiv_o, info_o = oracle.getrf_f64(n, a.T.reshape(-1), n)
+    assert info == 0 and np.array_equal(ipiv, ipiv_o)
+    assert np.max(np.abs(lu - lu_o)) <= 8 * n * EPS32 * np.max(np.abs(lu_o))
+
+
+@pytest.mark.parametrize("n", [64, 65, 200, 513, 1200])
+def test_lu_non_finite_entries_stay_in_their_column(n):
+    """Infinities and NaN in the last column reach that column of U only: the
+    other columns and the pivots are those of the same matrix with a finite
+    last column, bit for bit.  A column of NaN below its diagonal keeps its
+    own row as the pivot and is reported."""
+    rng = np.random.default_rng(52)
+    a = rng.uniform(-1, 1, (n, n)).astype(np.float32)
+    lu0, ipiv0, info0 = _factor(a, 0)[:3]
+    b = a.copy()
+    b[::3, -1] = np.inf
+    b[1::5, -1] = np.nan
+    lu1, ipiv1, info1 = _factor(b, 0)[:3]
+    assert np.array_equal(lu0[:, :-1], lu1[:, :-1])
+    assert np.array_equal(ipiv0[:-1], ipiv1[:-1])
+    c = a.copy()
+    c[:, 0] = np.nan
+    lu2, ipiv2, info2 = _factor(c, 0)[:3]
+    assert info2 == 1 and ipiv2[0] == 0
+    assert np.array_equal(lu2[0, 1:], a[0, 1:])
