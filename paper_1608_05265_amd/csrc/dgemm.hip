@@ -12,6 +12,8 @@
 #include "dgemm.hpp"
 #include "registry.hpp"
 
+#include <type_traits>
+
 namespace misgemm {
 
 typedef double doublex2 __attribute__((ext_vector_type(2)));
@@ -108,15 +110,59 @@ struct DArgs {
 // lane l is row l/16 + 4e of column l%16 (measured on the device with
 // one-hot operands: unlike the FP32 16x16 layout, a lane's four rows are
 // spaced by four).
+//
+// KW: the waves of a workgroup are KW groups that each cover the whole tile
+// and take 1/KW of the K steps of every block; their sums are added through
+// LDS at the end, in the order of the groups.
+//
+// What bounds it: the matrix cores (64 cycles per 16x16x4, 76.5 TFLOP/s over
+// the card), as long as nothing else of a wave stands between two of its
+// MFMAs for longer than one of them takes.  A wave issues in order, so
+// whatever comes in one lump -- the fragment reads of a K step, the LDS
+// stores and the loads of the next blocks -- leaves its matrix core idle.
+// Therefore every other instruction is dealt out between the MFMAs
+// (sched_group_barrier); the loads run two blocks ahead of their LDS stores
+// (two register sets), the stores one block ahead of their reads and the
+// reads one K step ahead of their MFMAs, across the barrier too, which
+// stands before the last K step of a block.  With two register sets, but
+// stores, barrier and reads in lumps at the ends of a block, 2048^3 took
+// 259-271 us; with one set 287-316 us; now 241 us (71 TFLOP/s).
 // ---------------------------------------------------------------------------
+template <int BM_, int BN_, int BK_, int WM_, int WN_, int KW_, int OCC_>
+struct DShape {
+    static constexpr int BM = BM_, BN = BN_, BK = BK_, WM = WM_, WN = WN_, KW = KW_, OCC = OCC_;
+    static constexpr int NWM = BM / WM, NWN = BN / WN, NT = 64 * NWM * NWN * KW;
+    static_assert(BM % WM == 0 && BN % WN == 0 && BK % (4 * KW) == 0, "whole waves and K steps");
+    static_assert(WM % 16 == 0 && WN % 16 == 0, "wave tile is made of 16x16 blocks");
+};
+
 template <class SH, bool TA, bool TB>
 struct F64Tile {
     static constexpr int RM = SH::WM / 16, RN = SH::WN / 16;
-    static_assert(SH::WM % 16 == 0 && SH::WN % 16 == 0 && SH::BK % 4 == 0, "16x16x4 blocks");
     using SA = StageF64<SH::BM, SH::BK, SH::NT, TA>;   // A is K-contiguous when transposed
     using SB = StageF64<SH::BN, SH::BK, SH::NT, !TB>;  // B is K-contiguous when not transposed
     static constexpr int STAGE = SA::ELEMS + SB::ELEMS;
-    static constexpr int LDS_BYTES = 2 * STAGE * 8;
+    static constexpr int SUMS = (SH::KW - 1) * SH::BM * SH::BN;
+    static constexpr int LDS_BYTES = (2 * STAGE > SUMS ? 2 * STAGE : SUMS) * 8;
+
+    struct Frags {
+        double a[RM], b[RN];
+        __device__ __forceinline__ void read(const double *As, const double *Bs, int kr)
+        {
+#pragma unroll
+            for (int i = 0; i < RM; ++i) a[i] = As[kr * SA::LD + i * 16];
+#pragma unroll
+            for (int j = 0; j < RN; ++j) b[j] = Bs[kr * SB::LD + j * 16];
+        }
+        __device__ __forceinline__ void multiply(doublex4 (&acc)[RM][RN]) const
+        {
+#pragma unroll
+            for (int i = 0; i < RM; ++i)
+#pragma unroll
+                for (int j = 0; j < RN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
+        }
+    };
 
     __device__ __forceinline__ static void epilogue(const DArgs &g, const doublex4 (&acc)[RM][RN],
                                                     int64_t row0, int64_t col0, int lane)
@@ -158,7 +204,7 @@ struct F64Tile {
     {
         double *lds = reinterpret_cast<double *>(smem);
         const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-        const int wm = wave % SH::NWM, wn = wave / SH::NWM;
+        const int wm = wave % SH::NWM, wn = wave / SH::NWM % SH::NWN, wk = wave / (SH::NWM * SH::NWN);
         const int kq = lane >> 4, r16 = lane & 15;
 
         doublex4 acc[RM][RN];
@@ -168,44 +214,86 @@ struct F64Tile {
             for (int j = 0; j < RN; ++j) acc[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
 
         const KBlocks<SH::BK> kb(g.k);
-        const int64_t ktiles = kb.count;
-        SA sa;
-        SB sb;
-        if (ktiles > 0) {
-            load_first<MODE>(sa, sb, g, m0, n0, kb, lds, lds + SA::ELEMS, tid);
-        }
+        const int blocks = (int)kb.count;  // op(A) alone would fill the memory before 2^31
+        SA sa[2];  // block b + 1 is in set b & 1
+        SB sb[2];
+        if (blocks > 0) load_first<MODE>(sa[0], sb[0], g, m0, n0, kb, lds, lds + SA::ELEMS, tid);
+        auto load = [&](int set, int b) {
+            sa[set].template load<MODE>(g.A, g.lda, m0, kb.at(b), g.m, g.k, tid);
+            sb[set].template load<MODE>(g.B, g.ldb, n0, kb.at(b), g.n, g.k, tid);
+        };
+        if (blocks > 1) load(0, 1);
+        if (blocks > 2) load(1, 2);
         __syncthreads();
-        for (int64_t kt = 0; kt < ktiles; ++kt) {
-            const double *cur = lds + (kt & 1) * STAGE;
-            double *nxt = lds + ((kt + 1) & 1) * STAGE;
-            const bool more = kt + 1 < ktiles;
-            if (more) {
-                const int64_t k0 = kb.at(kt + 1);
-                sa.template load<MODE>(g.A, g.lda, m0, k0, g.m, g.k, tid);
-                sb.template load<MODE>(g.B, g.ldb, n0, k0, g.n, g.k, tid);
+        constexpr int KS = SH::BK / 4 / SH::KW;  // K steps of this wave
+        static_assert(KS % 2 == 0, "a block starts with the fragments in f[0]");
+        const int kr = wk * KS * 4 + kq;
+        const int ao = wm * SH::WM + r16, bo = SA::ELEMS + wn * SH::WN + r16;
+        Frags f[2];
+        if (blocks > 0) f[0].read(lds + ao, lds + bo, kr);
+        // Block b of the K loop, in LDS stage `set`.  whole: blocks b + 1 to
+        // b + 3 exist, so the step is straight-line code.
+        auto step = [&](auto whole, int b, int set) {
+            constexpr bool WHOLE = decltype(whole)::value;
+            const double *cur = lds + set * STAGE;
+            double *nxt = lds + (set ^ 1) * STAGE;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                if (ks + 1 < KS) {
+                    f[(ks + 1) & 1].read(cur + ao, cur + bo, kr + (ks + 1) * 4);
+                } else {
+                    // every wave has stored its part of block b + 1 and has
+                    // read the last of block b
+                    __syncthreads();
+                    if (WHOLE || b + 1 < blocks) f[0].read(nxt + ao, nxt + bo, kr);
+                }
+                f[ks & 1].multiply(acc);
+                if (ks == 0 && (WHOLE || b + 1 < blocks)) {
+                    sa[set].template store<MODE>(nxt, m0, g.m, tid);
+                    sb[set].template store<MODE>(nxt + SA::ELEMS, n0, g.n, tid);
+                }
+                if (ks == (KS > 2 ? 1 : 0) && (WHOLE || b + 3 < blocks)) load(set, b + 3);
+#pragma unroll
+                for (int q = 0; q < RM * RN; ++q) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // an MFMA
+                    __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);  // LDS reads
+                    __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);  // an LDS write
+                    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // a load
+                    __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);  // VALU
+                }
+                __builtin_amdgcn_sched_barrier(0);
             }
-            const double *As = cur + wm * SH::WM + r16;
-            const double *Bs = cur + SA::ELEMS + wn * SH::WN + r16;
-#pragma unroll
-            for (int ks = 0; ks < SH::BK / 4; ++ks) {
-                const int kr = ks * 4 + kq;
-                double a[RM], b[RN];
-#pragma unroll
-                for (int i = 0; i < RM; ++i) a[i] = As[kr * SA::LD + i * 16];
-#pragma unroll
-                for (int j = 0; j < RN; ++j) b[j] = Bs[kr * SB::LD + j * 16];
+        };
+        int b = 0;
+        for (; b + 4 < blocks; b += 2) {
+            step(std::true_type{}, b, 0);
+            step(std::true_type{}, b + 1, 1);
+        }
+        for (; b + 1 < blocks; b += 2) {
+            step(std::false_type{}, b, 0);
+            step(std::false_type{}, b + 1, 1);
+        }
+        if (b < blocks) step(std::false_type{}, b, 0);
+        if (SH::KW > 1) {
+            __syncthreads();
+            doublex4 *sums = reinterpret_cast<doublex4 *>(lds) +
+                             (wm + wn * SH::NWM) * (RM * RN * 64) + lane;
+            constexpr int GROUP = SH::NWM * SH::NWN * RM * RN * 64;
+            if (wk > 0) {
 #pragma unroll
                 for (int i = 0; i < RM; ++i)
 #pragma unroll
                     for (int j = 0; j < RN; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j],
-                                                                          0, 0, 0);
-            }
-            if (more) {
-                sa.template store<MODE>(nxt, m0, g.m, tid);
-                sb.template store<MODE>(nxt + SA::ELEMS, n0, g.n, tid);
+                        sums[(wk - 1) * GROUP + (i * RN + j) * 64] = acc[i][j];
             }
             __syncthreads();
+            if (wk > 0) return;
+#pragma unroll
+            for (int w = 0; w < SH::KW - 1; ++w)
+#pragma unroll
+                for (int i = 0; i < RM; ++i)
+#pragma unroll
+                    for (int j = 0; j < RN; ++j) acc[i][j] += sums[w * GROUP + (i * RN + j) * 64];
         }
         epilogue(g, acc, m0 + wm * SH::WM, n0 + wn * SH::WN, lane);
     }
@@ -235,10 +323,19 @@ hipError_t launch_dgemm_shape(int ta, int tb, const DArgs &g, hipStream_t s)
     return hipGetLastError();
 }
 
-using DShapeL = Shape<128, 128, 16, 64, 64, 2>;
-using DShapeS = Shape<64, 64, 16, 32, 32, 2>;
-
-// Tile choice: 128x128 when that still gives every CU a tile, else 64x64.
+// Tile choice.  A call takes as long as its fullest CU: the tiles on it times
+// the operations of one, over the share of the matrix rate that the shape
+// reaches.  Measured shares, alone on a CU and with others on it: 64x64 0.87
+// and 0.93 (larger tiles are no faster: 128x64 237-264 us and 128x128
+// 241-252 us against 239-259 us at 2048^3); 32x32 in two K groups 0.67 and
+// 0.83; 32x32 in four K groups 0.7; 16x16 in eight K groups 0.4, eight waves
+// on a tile that one MFMA covers.  Both sides of the lines, in us:
+//   1024^3            64x64 36.6   32x32 40.7
+//   768^3             64x64 28.6   32x32 24.8
+//   1511x777x1003     64x64 69.9   32x32 50.7
+//   512x512x2048      32x32 27.9   in four groups 24.0   16x16 29.5
+//   256x256x4096      64x64 122    32x32 in four groups 39.9   16x16 21.9
+//   64x64x4096        64x64 122    32x32 in four groups 38.6   16x16 15.8
 hipError_t launch_dgemm_fp64(int ta, int tb, int64_t m, int64_t n, int64_t k, double alpha,
                              const double *A, int64_t lda, const double *B, int64_t ldb,
                              double beta, double *C, int64_t ldc, int cus, hipStream_t s)
@@ -248,9 +345,16 @@ hipError_t launch_dgemm_fp64(int ta, int tb, int64_t m, int64_t n, int64_t k, do
     g.A = A; g.B = B; g.C = C;
     g.lda = lda; g.ldb = ldb; g.ldc = ldc;
     g.alpha = alpha; g.beta = beta;
-    const int64_t big = ((m + 127) / 128) * ((n + 127) / 128);
-    if (big >= cus) return launch_dgemm_shape<DShapeL>(ta, tb, g, s);
-    return launch_dgemm_shape<DShapeS>(ta, tb, g, s);
+    auto cost = [&](int edge, double share) {
+        const int64_t tiles = ((m + edge - 1) / edge) * ((n + edge - 1) / edge);
+        return (double)((tiles + cus - 1) / cus) * edge * edge / share;
+    };
+    const bool alone = ((m + 31) / 32) * ((n + 31) / 32) <= cus;  // a 32x32 tile per CU
+    const double c64 = cost(64, 0.9), mid = cost(32, alone ? 0.7 : 0.78), c16 = cost(16, 0.4);
+    if (c16 < mid && c16 < c64) return launch_dgemm_shape<DShape<16, 16, 64, 16, 16, 8, 2>>(ta, tb, g, s);
+    if (c64 <= mid) return launch_dgemm_shape<DShape<64, 64, 16, 32, 32, 1, 2>>(ta, tb, g, s);
+    if (alone) return launch_dgemm_shape<DShape<32, 32, 64, 32, 16, 4, 2>>(ta, tb, g, s);
+    return launch_dgemm_shape<DShape<32, 32, 32, 32, 16, 2, 2>>(ta, tb, g, s);
 }
 
 // ---------------------------------------------------------------------------

@@ -134,3 +134,30 @@ def test_dgemm_degenerate_and_deterministic(dmode):
 
 def wl_dense(p):
     return p.C0.reshape(p.n, p.ldc).T[:p.m, :]
+
+
+# The FP64 tiles (64x64; 32x32 with K in two or four groups; 16x16 in eight)
+# by the sizes that choose them, and K loops of one to seven blocks with and
+# without a ragged one.  Integers: every partial sum is exact, in any order.
+@pytest.mark.parametrize("ta,tb", [("N", "N"), ("N", "T"), ("T", "N"), ("T", "T")])
+@pytest.mark.parametrize("m,n,ks", [
+    (1, 1, (1, 64, 129, 400)),
+    (17, 250, (3, 64, 128, 321, 385)),
+    (511, 497, (5, 64, 128, 190, 320)),
+    (769, 737, (7, 32, 64, 100, 160, 193)),
+    (1024, 1001, (2, 16, 33, 48, 64, 81, 112)),
+])
+def test_fp64_tiles_exact(ta, tb, m, n, ks):
+    import torch
+    mg = _mg()
+    rng = np.random.default_rng(64)
+    for k in ks:
+        a = rng.integers(-8, 9, size=(m, k)).astype(np.float64)
+        b = rng.integers(-8, 9, size=(k, n)).astype(np.float64)
+        c = rng.integers(-8, 9, size=(m, n)).astype(np.float64)
+        A = torch.from_numpy(np.ascontiguousarray(a if ta == "T" else a.T)).cuda()
+        B = torch.from_numpy(np.ascontiguousarray(b if tb == "T" else b.T)).cuda()
+        C = torch.from_numpy(np.ascontiguousarray(c.T)).cuda()
+        mg.dgemm(ta, tb, m, n, k, 2.0, A, k if ta == "T" else m, B, n if tb == "T" else k, -1.0, C, m)
+        got = C.cpu().numpy().T
+        assert np.array_equal(got, 2.0 * (a @ b) - c), (ta, tb, m, n, k)
