@@ -21,6 +21,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace misgemm {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
@@ -128,54 +130,64 @@ struct StageF32 {
     // at most at row rows - 4 and store() shifts a chunk that straddles the
     // last row into place.
     template <LoadMode MODE>
+    __device__ __forceinline__ void load_chunk(int s, const float *X, int64_t ld, int64_t r0,
+                                               int64_t k0, int64_t rows, int64_t kdim, int tid)
+    {
+        const int c = tid + s * NT;
+        if (CH % NT != 0 && c >= CH) return;
+        int r, kk;
+        chunk(c, r, kk);
+        int64_t gr = r0 + r;
+        const int64_t gk = k0 + kk;
+        if (MODE == MASKED) {
+            const float *p = KC ? X + gk + gr * ld : X + gr + gk * ld;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                v[s][e] = (KC ? gr < rows && gk + e < kdim : gk < kdim && gr + e < rows)
+                              ? p[e] : 0.0f;
+        } else {
+            if (MODE == EDGE) gr = min64(gr, rows - MIN_ROWS);
+            v[s] = *reinterpret_cast<const floatx4u *>(KC ? X + gk + gr * ld : X + gr + gk * ld);
+        }
+    }
+
+    template <LoadMode MODE>
     __device__ __forceinline__ void load(const float *X, int64_t ld, int64_t r0, int64_t k0,
                                          int64_t rows, int64_t kdim, int tid)
     {
 #pragma unroll
-        for (int s = 0; s < S; ++s) {
-            const int c = tid + s * NT;
-            if (CH % NT != 0 && c >= CH) break;
-            int r, kk;
-            chunk(c, r, kk);
-            int64_t gr = r0 + r;
-            const int64_t gk = k0 + kk;
-            if (MODE == MASKED) {
-                const float *p = KC ? X + gk + gr * ld : X + gr + gk * ld;
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    v[s][e] = (KC ? gr < rows && gk + e < kdim : gk < kdim && gr + e < rows)
-                                  ? p[e] : 0.0f;
-            } else {
-                if (MODE == EDGE) gr = min64(gr, rows - MIN_ROWS);
-                v[s] = *reinterpret_cast<const floatx4u *>(KC ? X + gk + gr * ld : X + gr + gk * ld);
-            }
-        }
+        for (int s = 0; s < S; ++s) load_chunk<MODE>(s, X, ld, r0, k0, rows, kdim, tid);
     }
 
     // r0, rows as in the load of the same MODE.
     template <LoadMode MODE>
+    __device__ __forceinline__ void store_chunk(int s, float *Xs, int64_t r0, int64_t rows,
+                                                int tid) const
+    {
+        const int c = tid + s * NT;
+        if (CH % NT != 0 && c >= CH) return;
+        int r, kk;
+        chunk(c, r, kk);
+        floatx4 x = v[s];
+        if (KC) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) Xs[(kk + e) * LD + r] = x[e];
+        } else {
+            if (MODE == EDGE) {
+                const int64_t past = r0 + r + 4 - rows;  // 1..3: the load started past rows early
+                if (past & 1) { x[0] = x[1]; x[1] = x[2]; x[2] = x[3]; }
+                if (past & 2) { x[0] = x[2]; x[1] = x[3]; }
+                if (past <= 0) x = v[s];
+            }
+            *reinterpret_cast<floatx4 *>(Xs + kk * LD + r) = x;
+        }
+    }
+
+    template <LoadMode MODE>
     __device__ __forceinline__ void store(float *Xs, int64_t r0, int64_t rows, int tid) const
     {
 #pragma unroll
-        for (int s = 0; s < S; ++s) {
-            const int c = tid + s * NT;
-            if (CH % NT != 0 && c >= CH) break;
-            int r, kk;
-            chunk(c, r, kk);
-            floatx4 x = v[s];
-            if (KC) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) Xs[(kk + e) * LD + r] = x[e];
-            } else {
-                if (MODE == EDGE) {
-                    const int64_t past = r0 + r + 4 - rows;  // 1..3: the load started past rows early
-                    if (past & 1) { x[0] = x[1]; x[1] = x[2]; x[2] = x[3]; }
-                    if (past & 2) { x[0] = x[2]; x[1] = x[3]; }
-                    if (past <= 0) x = v[s];
-                }
-                *reinterpret_cast<floatx4 *>(Xs + kk * LD + r) = x;
-            }
-        }
+        for (int s = 0; s < S; ++s) store_chunk<MODE>(s, Xs, r0, rows, tid);
     }
 };
 
@@ -413,164 +425,135 @@ __device__ __forceinline__ void load_first(SA &sa, SB &sb, const ARGS &g, int64_
 }
 
 // ---------------------------------------------------------------------------
-// The tile body: stage -> multiply -> epilogue for tile (m0, n0).
+// Small tiles for grids that leave CUs idle (a 256^3 problem has 16 tiles of
+// 64x64): every one of KW waves holds the whole BM x BN tile and takes every
+// KW-th K step of each staged block, so a tile's MFMA chain is KW times
+// shorter; at the end the waves' accumulators are added in wave order
+// through LDS and wave 0 stores.  The partial sums of one element therefore
+// run over the k steps s = w (mod KW) of wave w, and the result is the same
+// bits for every launch.
 // ---------------------------------------------------------------------------
-template <class SH, bool TA, bool TB, bool PF2 = false>
-struct F32Tile {
-    using SA = StageF32<SH::BM, SH::BK, SH::NT, TA>;   // A is K-contiguous when transposed
-    using SB = StageF32<SH::BN, SH::BK, SH::NT, !TB>;  // B is K-contiguous when not transposed
-    static constexpr int STAGE_FLOATS = SA::FLOATS + SB::FLOATS;
-    static constexpr int LDS_BYTES = 2 * STAGE_FLOATS * 4;
-    static constexpr int NT = SH::NT;
-
-    template <bool SPLIT = false>
-    __device__ __forceinline__ static void run(const GemmArgs &g, int64_t m0, int64_t n0,
-                                               char *smem)
-    {
-        if (m0 + SH::BM <= g.m && n0 + SH::BN <= g.n) run_impl<INTERIOR, SPLIT>(g, m0, n0, smem);
-        else if (g.m >= SA::MIN_ROWS && g.n >= SB::MIN_ROWS) run_impl<EDGE, SPLIT>(g, m0, n0, smem);
-        else run_impl<MASKED, SPLIT>(g, m0, n0, smem);
-    }
-
-    template <LoadMode MODE, bool SPLIT>
-    __device__ __forceinline__ static void run_impl(const GemmArgs &g, int64_t m0, int64_t n0,
-                                                    char *smem)
-    {
-        float *lds = reinterpret_cast<float *>(smem);
-        const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-        const int wm = wave % SH::NWM, wn = wave / SH::NWM;
-        const int half = lane >> 5, l32 = lane & 31;
-
-        floatx16 acc[SH::RM][SH::RN];
-#pragma unroll
-        for (int i = 0; i < SH::RM; ++i)
-#pragma unroll
-            for (int j = 0; j < SH::RN; ++j)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
-
-        const KBlocks<SH::BK> kb(g.k);
-        const int64_t ktiles = kb.count;
-        SA sa;
-        SB sb;
-        // PF2: a second register set takes the global loads of block kt+2
-        // at the top of block kt and moves into the first set at its end, so
-        // a load has two blocks of MFMA time to arrive instead of one
-        SA sa2;
-        SB sb2;
-        if (ktiles > 0) {
-            load_first<MODE>(sa, sb, g, m0, n0, kb, lds, lds + SA::FLOATS, tid);
-        }
-        if (PF2 && ktiles > 1) {
-            sa.template load<MODE>(g.A, g.lda, m0, kb.at(1), g.m, g.k, tid);
-            sb.template load<MODE>(g.B, g.ldb, n0, kb.at(1), g.n, g.k, tid);
-        }
-        __syncthreads();
-        for (int64_t kt = 0; kt < ktiles; ++kt) {
-            float *cur = lds + (kt & 1) * STAGE_FLOATS;
-            float *nxt = lds + ((kt + 1) & 1) * STAGE_FLOATS;
-            const bool more = kt + 1 < ktiles;
-            if (PF2) {
-                if (kt + 2 < ktiles) {
-                    const int64_t k0 = kb.at(kt + 2);
-                    sa2.template load<MODE>(g.A, g.lda, m0, k0, g.m, g.k, tid);
-                    sb2.template load<MODE>(g.B, g.ldb, n0, k0, g.n, g.k, tid);
-                }
-            } else if (more) {
-                const int64_t k0 = kb.at(kt + 1);
-                sa.template load<MODE>(g.A, g.lda, m0, k0, g.m, g.k, tid);
-                sb.template load<MODE>(g.B, g.ldb, n0, k0, g.n, g.k, tid);
-            }
-            const float *As = cur + wm * SH::WM + l32;
-            const float *Bs = cur + SA::FLOATS + wn * SH::WN + l32;
-#pragma unroll
-            for (int ks = 0; ks < SH::BK / 2; ++ks) {
-                const int kr = 2 * ks + half;  // lanes 0-31: even k, 32-63: odd k
-                float a[SH::RM], b[SH::RN];
-#pragma unroll
-                for (int i = 0; i < SH::RM; ++i) a[i] = As[kr * SA::LD + i * 32];
-#pragma unroll
-                for (int j = 0; j < SH::RN; ++j) b[j] = Bs[kr * SB::LD + j * 32];
-#pragma unroll
-                for (int i = 0; i < SH::RM; ++i)
-#pragma unroll
-                    for (int j = 0; j < SH::RN; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j],
-                                                                          0, 0, 0);
-            }
-            if (more) {
-                sa.template store<MODE>(nxt, m0, g.m, tid);
-                sb.template store<MODE>(nxt + SA::FLOATS, n0, g.n, tid);
-            }
-            if (PF2 && kt + 2 < ktiles) {
-                sa = sa2;
-                sb = sb2;
-            }
-            __syncthreads();
-        }
-        finish<SPLIT, SH::RM, SH::RN>(g, acc, m0 + wm * SH::WM, n0 + wn * SH::WN, tid, NT);
-    }
+template <int BM_, int BN_, int BK_, int KW_>
+struct WShape {
+    static constexpr int BM = BM_, BN = BN_, BK = BK_, KW = KW_, OCC = 1;
+    static constexpr int WM = BM, WN = BN, NWM = 1, NWN = 1, NW = KW, NT = 64 * KW;
+    static constexpr int RM = BM / 32, RN = BN / 32;
+    static_assert(BM % 32 == 0 && BN % 32 == 0, "the tile is made of 32x32 blocks");
 };
 
-// ---------------------------------------------------------------------------
-// Software-pipelined FP32 tile.  The operand fragments of K step s+1 are read
-// from LDS before the MFMAs of step s are issued (so a LDS round trip never
-// stalls the matrix core), and the LDS store of the next K block, whose
-// global loads were issued at the top of the block, sits between the MFMAs
-// of step STORE_STEP instead of after the last one.  The order is pinned
-// with sched_barrier.
-// ---------------------------------------------------------------------------
-template <class SH, bool TA, bool TB>
-struct F32PTile {
-    using SA = StageF32<SH::BM, SH::BK, SH::NT, TA>;
-    using SB = StageF32<SH::BN, SH::BK, SH::NT, !TB>;
-    static constexpr int STAGE_FLOATS = SA::FLOATS + SB::FLOATS;
-    static constexpr int LDS_BYTES = 2 * STAGE_FLOATS * 4;
-    static constexpr int NT = SH::NT;
-    static constexpr int RM = SH::RM, RN = SH::RN;
-    static constexpr int NKS = SH::BK / 2;           // MFMA K steps per block
-    static constexpr int STORE_STEP = NKS * 3 / 4;   // step that carries the store
-
-    __device__ __forceinline__ static void read_frag(const float *As, const float *Bs, int ks,
-                                                     int half, float (&a)[RM], float (&b)[RN])
-    {
-        const int kr = 2 * ks + half;  // lanes 0-31: even k, 32-63: odd k
+// Waves 1..KW-1 post their accumulators to LDS (lane-contiguous, so every
+// store and load of a wave is conflict-free), wave 0 adds them in wave
+// order.  The caller's K loop ended with a barrier, so the staging buffers
+// are free.
+template <int KW, int RM, int RN>
+__device__ __forceinline__ void wave_sum(floatx16 (&acc)[RM][RN], float *lds, int wave,
+                                         int lane)
+{
+    constexpr int PER = RM * RN * 16 * 64;
+    if (wave > 0) {
+        float *dst = lds + (wave - 1) * PER;
 #pragma unroll
-        for (int i = 0; i < RM; ++i) a[i] = As[kr * SA::LD + i * 32];
+        for (int i = 0; i < RM; ++i)
 #pragma unroll
-        for (int j = 0; j < RN; ++j) b[j] = Bs[kr * SB::LD + j * 32];
+            for (int j = 0; j < RN; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) dst[((i * RN + j) * 16 + e) * 64 + lane] = acc[i][j][e];
     }
-
-    template <LoadMode MODE>
-    __device__ __forceinline__ static void body(floatx16 (&acc)[RM][RN], const GemmArgs &g,
-                                                int64_t m0, int64_t n0, const float *cur,
-                                                float *nxt, const SA &sa, const SB &sb, int tid,
-                                                int wm, int wn, int half, int l32)
-    {
-        const float *As = cur + wm * SH::WM + l32;
-        const float *Bs = cur + SA::FLOATS + wn * SH::WN + l32;
-        float a[2][RM], b[2][RN];
-        read_frag(As, Bs, 0, half, a[0], b[0]);
-#pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) {
-            if (ks + 1 < NKS) {
-                read_frag(As, Bs, ks + 1, half, a[(ks + 1) & 1], b[(ks + 1) & 1]);
-                __builtin_amdgcn_sched_barrier(0);
-            }
+    __syncthreads();
+    if (wave == 0) {
+        for (int w = 1; w < KW; ++w) {
+            const float *src = lds + (w - 1) * PER;
 #pragma unroll
             for (int i = 0; i < RM; ++i)
 #pragma unroll
-                for (int j = 0; j < RN; ++j) {
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[ks & 1][i], b[ks & 1][j],
-                                                                      acc[i][j], 0, 0, 0);
-                    if (ks == STORE_STEP && i == 0 && j == 0) {
-                        __builtin_amdgcn_sched_barrier(0);
-                        sa.template store<MODE>(nxt, m0, g.m, tid);
-                        sb.template store<MODE>(nxt + SA::FLOATS, n0, g.n, tid);
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                }
+                for (int j = 0; j < RN; ++j)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e)
+                        acc[i][j][e] += src[((i * RN + j) * 16 + e) * 64 + lane];
         }
+    }
+}
+
+template <class SH>
+constexpr auto k_waves_of(int) -> decltype(SH::KW) { return SH::KW; }
+template <class SH>
+constexpr int k_waves_of(...) { return 1; }
+template <class SH>
+constexpr int k_waves() { return k_waves_of<SH>(0); }
+
+// ---------------------------------------------------------------------------
+// The FP32 tile: stage -> multiply -> epilogue for tile (m0, n0).
+//
+// What bounds it: the matrix cores (64 cycles per 32x32x2), as long as
+// nothing else of a wave stands between two of its MFMAs for longer than one
+// of them takes.  A wave issues in order: fragment reads, LDS stores, loads
+// and barrier in lumps cost a wave with one 32x32 block 550 of every 1575
+// cycles, at any number of LDS stages, load distance or waves per SIMD that
+// kept the lumps.  So the K loop is straight-line code (but for its last
+// blocks) in groups of four MFMAs or more, with everything else dealt out
+// between them: the fragments of the next group, across the barrier of a
+// block too, which stands before its last group; the LDS stores of the next
+// block and the loads of the one after (two after, in a second register set,
+// where a set is small).
+// TFLOP/s, lumped -> dealt out (NN): 1024x1024x4096 64x64x32 84 -> 109,
+// 2048^3 128x128x16 99 -> 132 and 64x64x32 110 -> 120, 4096^3 256x256x16
+// 136 -> 147, 8192x8192x256 128x128x16 109 -> 119.
+// ---------------------------------------------------------------------------
+template <class SH, bool TA, bool TB>
+struct F32Tile {
+    using SA = StageF32<SH::BM, SH::BK, SH::NT, TA>;   // A is K-contiguous when transposed
+    using SB = StageF32<SH::BN, SH::BK, SH::NT, !TB>;  // B is K-contiguous when not transposed
+    static constexpr int NT = SH::NT, RM = SH::RM, RN = SH::RN, KW = k_waves<SH>();
+    static constexpr int STAGE_FLOATS = SA::FLOATS + SB::FLOATS;
+    static constexpr int RED_FLOATS = (KW - 1) * RM * RN * 16 * 64;
+    static constexpr int LDS_BYTES =
+        (2 * STAGE_FLOATS > RED_FLOATS ? 2 * STAGE_FLOATS : RED_FLOATS) * 4;
+    static constexpr int STEPS = SH::BK / 2 / KW;  // K steps of a wave in a block
+    static constexpr int G = 4 / (RM * RN) < 1 ? 1 : 4 / (RM * RN) > STEPS / 2 ? STEPS / 2 : 4 / (RM * RN);
+    static constexpr int NG = STEPS / G;           // groups of G steps
+    static_assert(SH::BK % (2 * KW) == 0 && NG * G == STEPS && NG % 2 == 0, "whole pairs of groups");
+    static constexpr int CHUNKS = SA::S + SB::S;
+    // Register sets of loads.  Two are faster where they cost few registers
+    // (128x128x16 2048^3: 130 us against 140); 256x128x16 is 1-10% faster
+    // with one, 128x128x32 up to 20%, and 256x256x32 spills with two.
+    static constexpr int SETS = CHUNKS > 4 || RM * RN >= 8 ? 1 : 2;
+
+    struct Frags {
+        float a[G][RM], b[G][RN];
+        // ks: K step within the block, of k = 2 ks (lanes 0-31) and 2 ks + 1
+        __device__ __forceinline__ void read(const float *As, const float *Bs, int group, int half,
+                                             int wk)
+        {
+#pragma unroll
+            for (int s = 0; s < G; ++s) {
+                const int kr = 2 * ((group * G + s) * KW + wk) + half;
+#pragma unroll
+                for (int i = 0; i < RM; ++i) a[s][i] = As[kr * SA::LD + i * 32];
+#pragma unroll
+                for (int j = 0; j < RN; ++j) b[s][j] = Bs[kr * SB::LD + j * 32];
+            }
+        }
+        __device__ __forceinline__ void multiply(floatx16 (&acc)[RM][RN]) const
+        {
+#pragma unroll
+            for (int s = 0; s < G; ++s)
+#pragma unroll
+                for (int i = 0; i < RM; ++i)
+#pragma unroll
+                    for (int j = 0; j < RN; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[s][i], b[s][j],
+                                                                          acc[i][j], 0, 0, 0);
+        }
+    };
+
+    // The chunks of the next block are stored, and those of a later one
+    // loaded, in the groups before the barrier.
+    static constexpr int chunk_group(int c) { return c * (NG - 1) / CHUNKS; }
+    static constexpr int chunks_in(int group)
+    {
+        int n = 0;
+        for (int c = 0; c < CHUNKS; ++c) n += chunk_group(c) == group;
+        return n;
     }
 
     template <bool SPLIT = false>
@@ -588,7 +571,8 @@ struct F32PTile {
     {
         float *lds = reinterpret_cast<float *>(smem);
         const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-        const int wm = wave % SH::NWM, wn = wave / SH::NWM;
+        const int wm = wave % SH::NWM, wn = wave / SH::NWM % SH::NWN;
+        const int wk = KW > 1 ? wave / (SH::NWM * SH::NWN) : 0;
         const int half = lane >> 5, l32 = lane & 31;
 
         floatx16 acc[RM][RN];
@@ -600,27 +584,93 @@ struct F32PTile {
                 for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
 
         const KBlocks<SH::BK> kb(g.k);
-        const int64_t ktiles = kb.count;
-        SA sa;
-        SB sb;
-        if (ktiles > 0) {
-            load_first<MODE>(sa, sb, g, m0, n0, kb, lds, lds + SA::FLOATS, tid);
-        }
-        __syncthreads();
-        for (int64_t kt = 0; kt < ktiles; ++kt) {
-            const float *cur = lds + (kt & 1) * STAGE_FLOATS;
-            float *nxt = lds + ((kt + 1) & 1) * STAGE_FLOATS;
-            if (kt + 1 < ktiles) {
-                const int64_t k0 = kb.at(kt + 1);
-                sa.template load<MODE>(g.A, g.lda, m0, k0, g.m, g.k, tid);
-                sb.template load<MODE>(g.B, g.ldb, n0, k0, g.n, g.k, tid);
+        const int64_t blocks = kb.count;
+        SA sa[SETS];  // block b + 1 is in set b % SETS
+        SB sb[SETS];
+        if (blocks > 0) load_first<MODE>(sa[0], sb[0], g, m0, n0, kb, lds, lds + SA::FLOATS, tid);
+#pragma unroll
+        for (int d = 0; d < SETS; ++d)
+            if (blocks > 1 + d) {
+                sa[d].template load<MODE>(g.A, g.lda, m0, kb.at(1 + d), g.m, g.k, tid);
+                sb[d].template load<MODE>(g.B, g.ldb, n0, kb.at(1 + d), g.n, g.k, tid);
             }
-            // On the last block the store rewrites the idle buffer with data
-            // already consumed; nothing reads it afterwards.
-            body<MODE>(acc, g, m0, n0, cur, nxt, sa, sb, tid, wm, wn, half, l32);
-            __syncthreads();
+        __syncthreads();
+        const int ao = wm * SH::WM + l32, bo = SA::FLOATS + wn * SH::WN + l32;
+        Frags f[2];
+        if (blocks > 0) f[0].read(lds + ao, lds + bo, 0, half, wk);
+        // Block b of the K loop, in LDS stage b & 1 (given as a constant).
+        // whole: blocks b + 1 to b + 1 + SETS exist, so the step is
+        // straight-line code.
+        auto step = [&](auto whole, int64_t b, int stage) {
+            constexpr bool WHOLE = decltype(whole)::value;
+            const float *cur = lds + stage * STAGE_FLOATS;
+            float *nxt = lds + (stage ^ 1) * STAGE_FLOATS;
+            const int set = SETS == 2 ? stage : 0;
+            const bool store = WHOLE || b + 1 < blocks, load = WHOLE || b + 1 + SETS < blocks;
+            const int64_t k0 = kb.at(b + 1 + SETS);
+#pragma unroll
+            for (int q = 0; q < NG; ++q) {
+                if (q + 1 < NG) {
+                    f[(q + 1) & 1].read(cur + ao, cur + bo, q + 1, half, wk);
+                } else {
+                    // every wave has stored its part of block b + 1 and has
+                    // read the last of block b
+                    __syncthreads();
+                    if (store) f[0].read(nxt + ao, nxt + bo, 0, half, wk);
+                }
+                f[q & 1].multiply(acc);
+#pragma unroll
+                for (int c = 0; c < CHUNKS; ++c) {
+                    if (chunk_group(c) != q) continue;
+                    if (c < SA::S) {
+                        if (store) sa[set].template store_chunk<MODE>(c, nxt, m0, g.m, tid);
+                        if (load) sa[set].template load_chunk<MODE>(c, g.A, g.lda, m0, k0, g.m, g.k, tid);
+                    } else {
+                        if (store) sb[set].template store_chunk<MODE>(c - SA::S, nxt + SA::FLOATS, n0, g.n, tid);
+                        if (load) sb[set].template load_chunk<MODE>(c - SA::S, g.B, g.ldb, n0, k0, g.n, g.k, tid);
+                    }
+                }
+                constexpr int M = G * RM * RN;
+                constexpr int READS = (G * (RM + RN) + M - 1) / M;
+                const int writes = (chunks_in(q) * 4 + M - 1) / M, loads = (chunks_in(q) + M - 1) / M;
+                deal_out<M, READS>(writes, loads);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        int64_t b = 0;
+        if (MODE != MASKED) {
+            for (; b + 2 + SETS < blocks; b += 2) {
+                step(std::true_type{}, b, 0);
+                step(std::true_type{}, b + 1, 1);
+            }
+        }
+        for (; b + 1 < blocks; b += 2) {
+            step(std::false_type{}, b, 0);
+            step(std::false_type{}, b + 1, 1);
+        }
+        if (b < blocks) step(std::false_type{}, b, 0);
+        if constexpr (KW > 1) {
+            wave_sum<KW, RM, RN>(acc, lds, wave, lane);
+            if (wave != 0) return;
         }
         finish<SPLIT, RM, RN>(g, acc, m0 + wm * SH::WM, n0 + wn * SH::WN, tid, NT);
+    }
+
+    // sched_group_barrier takes constants only
+    template <int M, int READS>
+    __device__ __forceinline__ static void deal_out(int writes, int loads)
+    {
+#pragma unroll
+        for (int q = 0; q < M; ++q) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      // an MFMA
+            __builtin_amdgcn_sched_group_barrier(0x100, READS, 0);  // LDS reads
+            if (writes == 1) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+            else if (writes == 2) __builtin_amdgcn_sched_group_barrier(0x200, 2, 0);
+            else if (writes > 2) __builtin_amdgcn_sched_group_barrier(0x200, 4, 0);
+            if (loads == 1) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+            else if (loads > 1) __builtin_amdgcn_sched_group_barrier(0x020, 2, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);      // VALU
+        }
     }
 };
 
@@ -974,137 +1024,6 @@ struct X3PTile {
             __syncthreads();
         }
         finish<SPLIT, RM, RN>(g, acc, m0 + wm * SH::WM, n0 + wn * SH::WN, tid, NT);
-    }
-};
-
-// ---------------------------------------------------------------------------
-// Small tiles for grids that leave CUs idle (a 256^3 problem has 16 tiles of
-// 64x64): every one of KW waves holds the whole BM x BN tile and takes every
-// KW-th K step of each staged block, so a tile's MFMA chain is KW times
-// shorter; at the end the waves' accumulators are added in wave order
-// through LDS and wave 0 stores.  The partial sums of one element therefore
-// run over the k steps s = w (mod KW) of wave w, and the result is the same
-// bits for every launch.
-// ---------------------------------------------------------------------------
-template <int BM_, int BN_, int BK_, int KW_>
-struct WShape {
-    static constexpr int BM = BM_, BN = BN_, BK = BK_, KW = KW_, OCC = 1;
-    static constexpr int WM = BM, WN = BN, NWM = 1, NWN = 1, NW = KW, NT = 64 * KW;
-    static constexpr int RM = BM / 32, RN = BN / 32;
-    static_assert(BM % 32 == 0 && BN % 32 == 0, "the tile is made of 32x32 blocks");
-};
-
-// Waves 1..KW-1 post their accumulators to LDS (lane-contiguous, so every
-// store and load of a wave is conflict-free), wave 0 adds them in wave
-// order.  The caller's K loop ended with a barrier, so the staging buffers
-// are free.
-template <int KW, int RM, int RN>
-__device__ __forceinline__ void wave_sum(floatx16 (&acc)[RM][RN], float *lds, int wave,
-                                         int lane)
-{
-    constexpr int PER = RM * RN * 16 * 64;
-    if (wave > 0) {
-        float *dst = lds + (wave - 1) * PER;
-#pragma unroll
-        for (int i = 0; i < RM; ++i)
-#pragma unroll
-            for (int j = 0; j < RN; ++j)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) dst[((i * RN + j) * 16 + e) * 64 + lane] = acc[i][j][e];
-    }
-    __syncthreads();
-    if (wave == 0) {
-        for (int w = 1; w < KW; ++w) {
-            const float *src = lds + (w - 1) * PER;
-#pragma unroll
-            for (int i = 0; i < RM; ++i)
-#pragma unroll
-                for (int j = 0; j < RN; ++j)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e)
-                        acc[i][j][e] += src[((i * RN + j) * 16 + e) * 64 + lane];
-        }
-    }
-}
-
-template <class SH, bool TA, bool TB>
-struct F32WTile {
-    using SA = StageF32<SH::BM, SH::BK, SH::NT, TA>;
-    using SB = StageF32<SH::BN, SH::BK, SH::NT, !TB>;
-    static constexpr int KW = SH::KW, RM = SH::RM, RN = SH::RN, NT = SH::NT;
-    static constexpr int STEPS = SH::BK / 2;  // two k per v_mfma_f32_32x32x2_f32
-    static_assert(STEPS % KW == 0, "every wave takes the same number of k steps");
-    static constexpr int STAGE_FLOATS = SA::FLOATS + SB::FLOATS;
-    static constexpr int RED_FLOATS = (KW - 1) * RM * RN * 16 * 64;
-    static constexpr int LDS_BYTES =
-        (2 * STAGE_FLOATS > RED_FLOATS ? 2 * STAGE_FLOATS : RED_FLOATS) * 4;
-
-    template <bool SPLIT = false>
-    __device__ __forceinline__ static void run(const GemmArgs &g, int64_t m0, int64_t n0,
-                                               char *smem)
-    {
-        static_assert(!SPLIT, "no split-K variant");
-        if (m0 + SH::BM <= g.m && n0 + SH::BN <= g.n) run_impl<INTERIOR>(g, m0, n0, smem);
-        else if (g.m >= SA::MIN_ROWS && g.n >= SB::MIN_ROWS) run_impl<EDGE>(g, m0, n0, smem);
-        else run_impl<MASKED>(g, m0, n0, smem);
-    }
-
-    template <LoadMode MODE>
-    __device__ __forceinline__ static void run_impl(const GemmArgs &g, int64_t m0, int64_t n0,
-                                                    char *smem)
-    {
-        float *lds = reinterpret_cast<float *>(smem);
-        const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-        const int half = lane >> 5, l32 = lane & 31;
-        floatx16 acc[RM][RN];
-#pragma unroll
-        for (int i = 0; i < RM; ++i)
-#pragma unroll
-            for (int j = 0; j < RN; ++j)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
-        const KBlocks<SH::BK> kb(g.k);
-        const int64_t ktiles = kb.count;
-        SA sa;
-        SB sb;
-        if (ktiles > 0) {
-            load_first<MODE>(sa, sb, g, m0, n0, kb, lds, lds + SA::FLOATS, tid);
-        }
-        __syncthreads();
-        for (int64_t kt = 0; kt < ktiles; ++kt) {
-            float *cur = lds + (kt & 1) * STAGE_FLOATS;
-            float *nxt = lds + ((kt + 1) & 1) * STAGE_FLOATS;
-            const bool more = kt + 1 < ktiles;
-            if (more) {
-                const int64_t k0 = kb.at(kt + 1);
-                sa.template load<MODE>(g.A, g.lda, m0, k0, g.m, g.k, tid);
-                sb.template load<MODE>(g.B, g.ldb, n0, k0, g.n, g.k, tid);
-            }
-            const float *As = cur + l32;
-            const float *Bs = cur + SA::FLOATS + l32;
-#pragma unroll
-            for (int s = 0; s < STEPS / KW; ++s) {
-                const int kr = 2 * (s * KW + wave) + half;  // lanes 0-31: even k, 32-63: odd k
-                float a[RM], b[RN];
-#pragma unroll
-                for (int i = 0; i < RM; ++i) a[i] = As[kr * SA::LD + i * 32];
-#pragma unroll
-                for (int j = 0; j < RN; ++j) b[j] = Bs[kr * SB::LD + j * 32];
-#pragma unroll
-                for (int i = 0; i < RM; ++i)
-#pragma unroll
-                    for (int j = 0; j < RN; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j],
-                                                                          0, 0, 0);
-            }
-            if (more) {
-                sa.template store<MODE>(nxt, m0, g.m, tid);
-                sb.template store<MODE>(nxt + SA::FLOATS, n0, g.n, tid);
-            }
-            __syncthreads();
-        }
-        wave_sum<KW, RM, RN>(acc, lds, wave, lane);
-        if (wave == 0) epilogue<RM, RN>(g, acc, m0, n0, lane);
     }
 };
 
