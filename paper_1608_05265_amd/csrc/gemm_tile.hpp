@@ -435,7 +435,7 @@ __device__ __forceinline__ void load_first(SA &sa, SB &sb, const ARGS &g, int64_
 // ---------------------------------------------------------------------------
 template <int BM_, int BN_, int BK_, int KW_>
 struct WShape {
-    static constexpr int BM = BM_, BN = BN_, BK = BK_, KW = KW_, OCC = 1;
+    static constexpr int BM = BM_, BN = BN_, BK = BK_, KW = KW_, OCC = BM_ * BN_ > 1024 ? 2 : 4;
     static constexpr int WM = BM, WN = BN, NWM = 1, NWN = 1, NW = KW, NT = 64 * KW;
     static constexpr int RM = BM / 32, RN = BN / 32;
     static_assert(BM % 32 == 0 && BN % 32 == 0, "the tile is made of 32x32 blocks");

@@ -52,18 +52,24 @@ ConfigEntry make_f32(const char *name)
 // equal shapes are one kernel.
 void register_f32(std::vector<ConfigEntry> &out)
 {
+    // The last number of a shape holds its batched kernel, which has the four
+    // transposes' loops in it, to the registers of that many waves per SIMD:
+    // left alone it took up to 306 and ran one (batches of 16..1024 in steps
+    // of 16, 64x64x16: 1771 -> 1620 us; 128x128x16: 2006 -> 1535 us; of
+    // 24..500: 187 -> 115 us).  Three waves
+    // for 128x64x16 cost it 2048^3 136 -> 144 us.
     out.push_back(make_f32<F32, Shape<256, 256, 16, 128, 64>, false>("fp32p_256x256x16_w128x64"));
     out.push_back(make_f32<F32, Shape<256, 256, 32, 128, 64>, false>("fp32p_256x256x32_w128x64"));
     out.push_back(make_f32<F32, Shape<256, 128, 16, 128, 64, 2>, false>("fp32p_256x128x16_w128x64"));
-    out.push_back(make_f32<F32, Shape<128, 128, 16, 64, 64>, true, true>("fp32p_128x128x16_w64x64"));
+    out.push_back(make_f32<F32, Shape<128, 128, 16, 64, 64, 2>, true, true>("fp32p_128x128x16_w64x64"));
     out.push_back(make_f32<F32, Shape<128, 128, 32, 64, 64>, true>("fp32p_128x128x32_w64x64"));
-    out.push_back(make_f32<F32, Shape<64, 64, 32, 32, 32>, true, true>("fp32p_64x64x32_w32x32"));
-    out.push_back(make_f32<F32, Shape<128, 128, 16, 64, 64>, true, true>("fp32_128x128x16_w64x64"));
-    out.push_back(make_f32<F32, Shape<128, 64, 16, 64, 32>, true>("fp32_128x64x16_w64x32"));
-    out.push_back(make_f32<F32, Shape<64, 64, 16, 32, 32>, true, true>("fp32_64x64x16_w32x32"));
-    out.push_back(make_f32<F32, Shape<64, 64, 16, 32, 32>, true, true>("fp32q_64x64x16_w32x32"));
-    out.push_back(make_f32<F32, Shape<128, 128, 16, 64, 64>, true, true>("fp32q_128x128x16_w64x64"));
-    out.push_back(make_f32<F32, Shape<128, 64, 16, 64, 32>, true>("fp32q_128x64x16_w64x32"));
+    out.push_back(make_f32<F32, Shape<64, 64, 32, 32, 32, 2>, true, true>("fp32p_64x64x32_w32x32"));
+    out.push_back(make_f32<F32, Shape<128, 128, 16, 64, 64, 2>, true, true>("fp32_128x128x16_w64x64"));
+    out.push_back(make_f32<F32, Shape<128, 64, 16, 64, 32, 2>, true>("fp32_128x64x16_w64x32"));
+    out.push_back(make_f32<F32, Shape<64, 64, 16, 32, 32, 4>, true, true>("fp32_64x64x16_w32x32"));
+    out.push_back(make_f32<F32, Shape<64, 64, 16, 32, 32, 4>, true, true>("fp32q_64x64x16_w32x32"));
+    out.push_back(make_f32<F32, Shape<128, 128, 16, 64, 64, 2>, true, true>("fp32q_128x128x16_w64x64"));
+    out.push_back(make_f32<F32, Shape<128, 64, 16, 64, 32, 2>, true>("fp32q_128x64x16_w64x32"));
     // small tiles, four waves splitting each tile's K steps
     out.push_back(make_f32<F32, WShape<64, 64, 32, 4>, true>("fp32w_64x64x32_k4"));
     out.push_back(make_f32<F32, WShape<32, 32, 32, 4>, true>("fp32w_32x32x32_k4"));
