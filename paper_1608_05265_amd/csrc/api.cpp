@@ -7,6 +7,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <array>
 #include <map>
 #include <mutex>
 #include <string>
@@ -126,39 +127,176 @@ int tuned_config(int mode, int ta, int tb, int64_t m, int64_t n, int64_t k, bool
     return best;
 }
 
-// Built-in choice: the largest tile that still gives every CU at least one
-// tile (packed configurations first on equal area, when allowed); below that
-// the smallest tile (fewest idle CUs).
-int heuristic_config(int mode, int64_t m, int64_t n, int64_t k, int cus, bool allow_packed)
+// ---------------------------------------------------------------------------
+// Built-in choice: the configuration and the number of K splits with the
+// smallest predicted time.  A call's fullest CU holds
+//   r = ceil(tiles * splits / CUs)
+// workgroups, each of w = the time its share of K takes at the rate a CU has
+// on paper (150 TFLOP/s over 256 CUs in FP32, 240 in the split form).  They
+// take w r / full together where the shape fills the CU, and at least
+// w / alone each (`resident` at a time) where it does not; starting the
+// launch takes `start` us and reading and writing C `store` us per 100 x 100
+// of it.  The five numbers of a row were fitted to the times of every
+// configuration on 95 shapes (64 to 6144 a side, rank-k updates of up to
+// 16384 x 16384, K up to 16384, all transposes; three quarters of them
+// random), the 256-wide FP32 rows and `top` to 8192^3 as well.  Over these the choice is 1.4 % (FP32), 0.7 % (split form) and
+// 0.6 % (split form with a caller's workspace) slower than the fastest
+// configuration of each, at worst 20 %.  The largest tile that gives every
+// CU one, the nearest of the tuned squares before that, and two workgroups
+// per CU by splits chose, in us: 1536x1536x8192 515 for 385, 3000x3000x300
+// 93 for 57, 10144x8795x64 249 for 207, 1511x777x1003 44 for 37.
+// ---------------------------------------------------------------------------
+struct CostRow {
+    const char *name;
+    int resident;
+    double start, full, alone, store;
+    double pack;  // TB/s at which a packed row's operands are packed, else 0
+    double top;   // share of the paper rate that long K loops reach, where
+                  // `full` was fitted beyond it (with a large `store`), else 0
+    bool batch;   // a candidate for batched plans
+};
+const CostRow FP32_ROWS[] = {
+    {"fp32r_16x16x32_r8", 1, 7.625, 1.158, 0.436, 11.233, 0, 0, false},
+    {"fp32r_16x16x64_r4", 1, 7.0, 0.773, 0.358, 7.699, 0, 0, false},
+    {"fp32r_32x32x64_r4", 1, 6.316, 0.977, 0.512, 13.086, 0, 0, false},
+    {"fp32w_32x32x32_k4", 2, 7.524, 0.764, 0.613, 4.133, 0, 0, true},
+    {"fp32q_64x64x16_w32x32", 2, 6.077, 0.888, 0.823, 2.616, 0, 0, true},
+    {"fp32p_64x64x32_w32x32", 2, 5.614, 0.882, 0.855, 3.48, 0, 0, false},
+    {"fp32q_128x64x16_w64x32", 2, 4.442, 0.947, 0.886, 2.741, 0, 0, true},
+    {"fp32q_128x128x16_w64x64", 2, 3.83, 1.094, 0.965, 3.422, 0, 0.965, true},
+    {"fp32p_256x128x16_w128x64", 2, 2.034, 1.1, 0.953, 4.074, 0, 0.981, false},
+    {"fp32p_256x256x16_w128x64", 1, 1.0, 1.0, 1.0, 4.0, 0, 0, false},
+};
+const CostRow X3_ROWS[] = {
+    {"x3r_16x16x32_r8", 2, 6.861, 0.228, 0.225, 11.325, 0, 0, false},
+    {"x3r_32x32x64_r4", 2, 4.705, 0.358, 0.311, 27.08, 0, 0, false},
+    {"x3w_32x32x64_k4", 2, 5.03, 0.326, 0.205, 11.597, 0, 0, false},
+    {"x3_64x64x32_w32x32", 2, 4.341, 0.537, 0.408, 4.152, 0, 0, true},
+    {"x3q_128x128x16_w64x64", 2, 2.016, 0.767, 0.445, 3.41, 0, 0, true},
+    {"x3d_128x128x32_w64x64", 1, 1.0, 0.658, 0.657, 6.458, 0, 0, false},
+    {"x3f_256x256x16_w64x128", 1, 1.0, 1.089, 1.065, 4.523, 0, 0, false},
+    {"x3dl_256x256x16_w64x128", 1, 1.0, 1.245, 1.206, 4.962, 3.741, 0, false},
+    {"x3dl_128x128x16_w64x64", 2, 5.934, 0.968, 0.705, 4.101, 4.917, 0, false},
+    {"x3dl_64x64x16_w32x32", 2, 10.307, 0.749, 0.381, 3.163, 3.321, 0, false},
+    {"x3k_256x256x16_w64x128", 1, 1.0, 1.123, 1.172, 4.982, 3.429, 0, false},
+    {"x3k_128x128x16_w64x64", 2, 8.62, 0.976, 0.767, 2.988, 4.345, 0, false},
+    {"x3k_64x64x16_w32x32", 3, 10.257, 0.716, 0.288, 2.98, 4.612, 0, false},
+};
+// Splitting K: the second launch, the partial sums written and read (TB/s)
+// and added (us per split of a 64 x 64 tile).
+struct SplitCost {
+    double launch, rate, add;
+};
+const SplitCost SPLIT_COST[2] = {{1.97, 4.14, 0.86}, {2.46, 3.95, 0.89}};
+const double PAPER_RATE[2] = {150e6 / 256, 240e6 / 256};  // FLOP per us and CU
+
+struct ModelConfig {
+    CostRow row;
+    int id;
+};
+const std::vector<ModelConfig> &model_configs(int mode)
 {
-    (void)k;
-    const auto &t = configs();
-    int best = -1;
-    int64_t best_key = -1;
-    int smallest = -1;
-    int64_t smallest_area = INT64_MAX;
-    for (size_t i = 0; i < t.size(); ++i) {
-        const misgemm_config_desc &d = t[i].desc;
-        if (d.mode != mode || (d.packed && !allow_packed)) continue;
-        const int64_t area = (int64_t)d.bm * d.bn;
-        const int64_t key = 2 * area + (d.packed ? 1 : 0);
-        const int64_t tiles = ((m + d.bm - 1) / d.bm) * ((n + d.bn - 1) / d.bn);
-        if (tiles >= cus && key > best_key) { best_key = key; best = (int)i; }
-        if (area < smallest_area) { smallest_area = area; smallest = (int)i; }
-    }
-    return best >= 0 ? best : smallest;
+    static const std::array<std::vector<ModelConfig>, 2> all = [] {
+        std::array<std::vector<ModelConfig>, 2> r;
+        for (const CostRow &c : FP32_ROWS) r[0].push_back({c, find_config(c.name)});
+        for (const CostRow &c : X3_ROWS) r[1].push_back({c, find_config(c.name)});
+        return r;
+    }();
+    return all[mode];
 }
 
+// allow_split: whether partial sums have a place to go.  splits: 1 for whole K.
+int model_config(int mode, int64_t m, int64_t n, int64_t k, int cus, bool allow_packed,
+                 bool allow_split, int *splits)
+{
+    const auto &table = configs();
+    int best = -1;
+    double best_us = 1e300;
+    *splits = 1;
+    for (const ModelConfig &mc : model_configs(mode)) {
+        if (mc.id < 0) continue;
+        const misgemm_config_desc &d = table[mc.id].desc;
+        if (d.packed && !allow_packed) continue;
+        const CostRow &c = mc.row;
+        const double tiles = (double)((m + d.bm - 1) / d.bm) * (double)((n + d.bn - 1) / d.bn);
+        const double area = (double)d.bm * d.bn;
+        const int64_t blocks = (k + d.bk - 1) / d.bk;
+        // a split of fewer than four K blocks, more than four workgroups per
+        // CU or tiles that fill the card anyway never paid
+        const bool can_split = allow_split && table[mc.id].splitk[0][0] != nullptr &&
+                               tiles < 1.5 * cus;
+        for (int s = 1; s <= 16; s *= 2) {
+            if (s > 1 && (!can_split || blocks < 4 * s || tiles * s > 4.0 * cus)) break;
+            const double per = (double)((blocks + s - 1) / s) * d.bk;
+            const double r = ceil(tiles * s / cus), w = per * area * 2.0 / PAPER_RATE[mode];
+            double us = c.start + fmax(r * w / c.full, w / c.alone * fmax(1.0, r / c.resident));
+            const double least = c.top > 0 ? r * w / c.top : 0;
+            if (s == 1) {
+                us += r * c.store * area * 1e-4;
+                if (c.pack > 0) us += (double)(m + n) * k * 10.0 / (c.pack * 1e6);
+            } else {
+                const SplitCost &sc = SPLIT_COST[mode];
+                us += sc.launch + s * tiles * area * 8.0 / (sc.rate * 1e6) + sc.add * s * area / 4096.0;
+            }
+            us = fmax(us, least);
+            if (us < best_us) {
+                best_us = us;
+                best = mc.id;
+                *splits = s;
+            }
+        }
+    }
+    return best;
+}
+
+// The same for a batched plan, whose workgroups take tiles until none is left:
+// the work of all tiles spread over the CUs, and at its end the longest tile,
+// which starts late enough to cost 0.6 of itself.  Against the times of every
+// configuration on 24 plans (32 to 512 problems of 24 to 1024 a side) the
+// choice is at most 15 % from the fastest and on average 3 %.  A plan in two
+// concurrent parts by problem size, which chose before, pays a fork and a join
+// on the host and two launches: 64 problems of 24..568 80 us for 52, 33 of
+// 24..500 85 for 32, 126 of 24..220 in the split form 53 for 18; at 512 of
+// 32..1024 it is 1 % faster (1470 for 1487).
+int batch_model_config(const misgemm_problem *problems, int64_t count, int mode, int cus)
+{
+    const auto &table = configs();
+    int best = -1;
+    double best_us = 1e300;
+    for (const ModelConfig &mc : model_configs(mode)) {
+        const CostRow &c = mc.row;
+        if (mc.id < 0 || !c.batch || !has_batch(table[mc.id])) continue;
+        const misgemm_config_desc &d = table[mc.id].desc;
+        const double area = (double)d.bm * d.bn, c_us = c.store * area * 1e-4;
+        double work = 0, longest = 0;
+        for (int64_t i = 0; i < count; ++i) {
+            const misgemm_problem &p = problems[i];
+            const double tiles =
+                (double)((p.m + d.bm - 1) / d.bm) * (double)((p.n + d.bn - 1) / d.bn);
+            const double w =
+                (double)((p.k + d.bk - 1) / d.bk) * d.bk * area * 2.0 / PAPER_RATE[mode];
+            work += tiles * (w / c.full + c_us);
+            if (tiles > 0) longest = fmax(longest, w / c.alone + c_us);
+        }
+        const double us = c.start + fmax(work / cus + 0.6 * longest, longest);
+        if (us < best_us) {
+            best_us = us;
+            best = mc.id;
+        }
+    }
+    return best;
+}
+
+// The nearest tuned entry, else the model's choice.
 int select_config(int mode, int ta, int tb, int64_t m, int64_t n, int64_t k, int cus,
-                  bool allow_packed, int *group_m, int *splits)
+                  bool allow_packed, bool allow_split, int *group_m, int *splits)
 {
     *group_m = GROUP_M_DEFAULT;
     *splits = 0;
     const int c = tuned_config(mode, ta, tb, m, n, k, allow_packed, group_m, splits);
     if (c >= 0) return c;
     *group_m = GROUP_M_DEFAULT;
-    *splits = 0;
-    return heuristic_config(mode, m, n, k, cus, allow_packed);
+    return model_config(mode, m, n, k, cus, allow_packed, allow_split, splits);
 }
 
 // ---------------------------------------------------------------------------
@@ -386,7 +524,8 @@ int run_sgemm(char transa, char transb, int64_t m, int64_t n, int64_t k, float a
     int cfg = config_id;
     int splits = splits_req;
     int tuned_splits = 0;
-    if (cfg < 0) cfg = select_config(mode, ta, tb, m, n, k, dev->cus, packable, &gm, &tuned_splits);
+    if (cfg < 0) cfg = select_config(mode, ta, tb, m, n, k, dev->cus, packable,
+                                     policy == WS_LIBRARY && splits_req == 0, &gm, &tuned_splits);
     if (cfg < 0) return MISGEMM_E_BAD_CONFIG;
     if (splits == 0) splits = tuned_splits;
     void *ws = nullptr;
@@ -402,7 +541,8 @@ int run_sgemm(char transa, char transb, int64_t m, int64_t n, int64_t k, float a
             if (config_id >= 0 && policy == WS_LIBRARY) return wrc != 0 ? wrc : MISGEMM_E_CAPTURING;
             if (wrc != 0 && wrc != MISGEMM_E_CAPTURING) return wrc;
             // no workspace (capturing, or none given): a non-packed config
-            cfg = heuristic_config(mode, m, n, k, dev->cus, false);
+            int whole = 1;
+            cfg = model_config(mode, m, n, k, dev->cus, false, false, &whole);
             gm = group_m > 0 ? group_m : GROUP_M_DEFAULT;
             splits = splits_req;
         }
@@ -879,7 +1019,7 @@ int misgemm_select_config(char transa, char transb, int64_t m, int64_t n, int64_
     int cus = 256;
     if (current_device(&dev) == 0) cus = dev->cus;
     int gm = 0, splits = 0;
-    return select_config(mode, ta, tb, m, n, k, cus, false, &gm, &splits);
+    return select_config(mode, ta, tb, m, n, k, cus, false, true, &gm, &splits);
 }
 
 int misgemm_load_tuning(const char *path)
@@ -980,32 +1120,11 @@ int misgemm_batch_plan(const misgemm_problem *problems, int64_t count, int mode,
     if (rc != 0) return rc;
     const auto &table = configs();
 
-    // configuration: explicit, else the heuristic/tuned choice for the
-    // problem carrying the most work, among configs with a batched variant
+    // configuration: explicit, else the tuning table's, else the model's
     int cfg = config_id;
-    if (cfg >= 0) {
-        if (cfg >= (int)table.size() || table[cfg].desc.mode != mode || !has_batch(table[cfg]))
-            return MISGEMM_E_BAD_CONFIG;
-    } else {
-        {
-            std::lock_guard<std::mutex> lock(g_tune_mutex);
-            cfg = g_batch_config[mode];
-        }
-        int64_t smallest = INT64_MAX;
-        for (size_t i = 0; i < table.size(); ++i) {
-            const misgemm_config_desc &d = table[i].desc;
-            if (d.mode != mode || !has_batch(table[i])) continue;
-            // default: the 128x128 tile if compiled, else the smallest
-            const int64_t area = (int64_t)d.bm * d.bn;
-            if (d.bm == 128 && d.bn == 128 && cfg < 0) cfg = (int)i;
-            if (area < smallest) smallest = area;
-        }
-        if (cfg < 0)
-            for (size_t i = 0; i < table.size(); ++i)
-                if (table[i].desc.mode == mode && has_batch(table[i]) &&
-                    (int64_t)table[i].desc.bm * table[i].desc.bn == smallest) { cfg = (int)i; break; }
-        if (cfg < 0) return MISGEMM_E_BAD_CONFIG;
-    }
+    if (cfg >= 0 &&
+        (cfg >= (int)table.size() || table[cfg].desc.mode != mode || !has_batch(table[cfg])))
+        return MISGEMM_E_BAD_CONFIG;
     for (int64_t i = 0; i < count; ++i) {
         const misgemm_problem &p = problems[i];
         rc = validate(p.transa, p.transb, p.m, p.n, p.k, p.alpha, p.A, p.lda, p.B, p.ldb, p.C,
@@ -1014,6 +1133,14 @@ int misgemm_batch_plan(const misgemm_problem *problems, int64_t count, int mode,
             if (bad_index) *bad_index = i;
             return rc;
         }
+    }
+    if (cfg < 0) {
+        {
+            std::lock_guard<std::mutex> lock(g_tune_mutex);
+            cfg = g_batch_config[mode];
+        }
+        if (cfg < 0) cfg = batch_model_config(problems, count, mode, dev->cus);
+        if (cfg < 0) return MISGEMM_E_BAD_CONFIG;
     }
     // A tuned two-part rule (no explicit config): the problems with m and n
     // at or above the threshold on one configuration, the rest on another,
