@@ -77,11 +77,11 @@ typedef enum {
  *   -8 lda, -9 B NULL, -10 ldb, -12 C NULL, -13 ldc, -14 mode.
  * The kernel configuration (tile shape, wave layout, split-K factor) comes
  * from the loaded tuning table when it holds an entry for the shape, else
- * from built-in heuristics; misgemm_sgemm never picks a packed bf16x3
+ * from a built-in cost model; misgemm_sgemm never picks a packed bf16x3
  * configuration (those need a workspace: misgemm_sgemm_ws).  One choice uses
  * scratch memory that the library owns per (device, stream) -- calls on one
  * stream share it in stream order, calls on different streams never share
- * it: split-K, which the table or the heuristics pick when the C tiles alone
+ * it: split-K, which the table or the model pick when the C tiles alone
  * would leave CUs idle (each of `splits` workgroups per tile computes a K
  * range and stores its partial tile, splits * tiles * bm * bn * 4 bytes; a
  * second kernel adds the partials in split order and applies alpha/beta, so
@@ -224,7 +224,7 @@ int misgemm_config_info(int id, misgemm_config_desc *out);
 
 /*
  * Which configuration misgemm_sgemm would pick for this problem (tuning
- * table first, then heuristics; never a packed one), or a negative argument
+ * table first, then the cost model; never a packed one), or a negative argument
  * error.
  */
 int misgemm_select_config(char transa, char transb, int64_t m, int64_t n, int64_t k,
@@ -240,7 +240,7 @@ int misgemm_select_config(char transa, char transb, int64_t m, int64_t n, int64_
  * a split-K variant) and
  *     batch <mode> <config_name>
  * (the default configuration of batched plans); '#' starts a comment line.
- * path == NULL clears the table and returns to the built-in heuristics.
+ * path == NULL clears the table and returns to the built-in cost model.
  * The table is replaced only when the whole file parses.  Not thread-safe
  * with concurrent calls of the other entry points.
  * Error: MISGEMM_E_TUNING_FILE.
@@ -286,11 +286,9 @@ int misgemm_dgemm(char transa, char transb, int64_t m, int64_t n, int64_t k,
  * dividing that column, as LAPACK's getrf does).  Recursive right-looking
  * algorithm: the trailing updates and the off-diagonal parts of the
  * triangular solves are sgemm calls in `mode` (MISGEMM_FP32 or
- * MISGEMM_BF16X3), except the smallest ones, between two sibling leaves,
- * which the right leaf applies itself in FP32; leaf panels of 8 columns (4
- * when taller than 8192 rows) are factored by one workgroup, and each
- * leaf's interchanges are applied to the rest of the matrix right after
- * it.
+ * MISGEMM_BF16X3); panels of 64 columns are factored in one launch each by
+ * one or more workgroups, and each panel's interchanges are applied to the
+ * rest of the matrix right after it.
  * Asynchronous on `stream`; uses the library scratch of misgemm_sgemm.
  * Errors: -1 n, -2 A, -3 lda, -4 ipiv, -5 info, -6 mode (before any launch).
  */

@@ -674,6 +674,12 @@ struct F32Tile {
     }
 };
 
+// The split-form tile.  Its bound is the issue of one wave: per block a thread
+// splits 16 or 32 elements (some 90 or 180 VALU instructions) beside 12 or 48
+// MFMAs of 32 cycles.  As in the FP32 tile the K loop is straight-line code
+// with the splitting, the LDS accesses and the loads dealt out between the
+// MFMAs; in lumps behind them, us before -> after: 2048^3 128x128x32 130 ->
+// 111 (156 TFLOP/s), 1024x1024x4096 TN 64x64x32 115 -> 97.
 template <class SH, bool TA, bool TB, bool ACC2>
 struct X3Tile {
     using SA = StageX3<SH::BM, SH::BK, SH::NT, TA>;
@@ -682,6 +688,48 @@ struct X3Tile {
     static constexpr int STAGE_HALVES = SA::HALVES + SB::HALVES;
     static constexpr int LDS_BYTES = 2 * STAGE_HALVES * 2;
     static constexpr int NT = SH::NT;
+
+    static constexpr int NKS = SH::BK / 16;  // K steps of a block
+    static_assert(NKS % 2 == 0, "a block starts with the fragments in f[0]");
+    // register sets of loads: two where a set is small
+    static constexpr int SETS = SA::S + SB::S > 2 ? 1 : 2;
+
+    struct Frags {
+        bf16x8 a[SH::RM][3], b[SH::RN][3];
+        __device__ __forceinline__ void read(const __bf16 *As, const __bf16 *Bs, int ks)
+        {
+#pragma unroll
+            for (int i = 0; i < SH::RM; ++i)
+#pragma unroll
+                for (int t = 0; t < 3; ++t)
+                    a[i][t] = *reinterpret_cast<const bf16x8 *>(As + t * SA::PART +
+                                                                i * 32 * SA::LD + ks * 16);
+#pragma unroll
+            for (int j = 0; j < SH::RN; ++j)
+#pragma unroll
+                for (int t = 0; t < 3; ++t)
+                    b[j][t] = *reinterpret_cast<const bf16x8 *>(Bs + t * SB::PART +
+                                                                j * 32 * SB::LD + ks * 16);
+        }
+        __device__ __forceinline__ void
+        multiply(floatx16 (&acc)[SH::RM][SH::RN],
+                 floatx16 (&lo)[ACC2 ? SH::RM : 1][ACC2 ? SH::RN : 1]) const
+        {
+#pragma unroll
+            for (int i = 0; i < SH::RM; ++i)
+#pragma unroll
+                for (int j = 0; j < SH::RN; ++j) {
+                    // smallest terms first; (0,0) is the leading product
+                    floatx16 &small = ACC2 ? lo[ACC2 ? i : 0][ACC2 ? j : 0] : acc[i][j];
+                    small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][0], b[j][2], small, 0, 0, 0);
+                    small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][1], b[j][1], small, 0, 0, 0);
+                    small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][2], b[j][0], small, 0, 0, 0);
+                    small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][0], b[j][1], small, 0, 0, 0);
+                    small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][1], b[j][0], small, 0, 0, 0);
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][0], b[j][0], acc[i][j], 0, 0, 0);
+                }
+        }
+    };
 
     template <bool SPLIT = false>
     __device__ __forceinline__ static void run(const GemmArgs &g, int64_t m0, int64_t n0,
@@ -719,59 +767,73 @@ struct X3Tile {
         }
 
         const KBlocks<SH::BK> kb(g.k);
-        const int64_t ktiles = kb.count;
-        SA sa;
-        SB sb;
-        if (ktiles > 0) {
-            load_first<MODE>(sa, sb, g, m0, n0, kb, lds, lds + SA::HALVES, tid);
-        }
+        const int64_t blocks = kb.count;
+        SA sa[SETS];  // block b + 1 is in set b % SETS
+        SB sb[SETS];
+        if (blocks > 0) load_first<MODE>(sa[0], sb[0], g, m0, n0, kb, lds, lds + SA::HALVES, tid);
+#pragma unroll
+        for (int d = 0; d < SETS; ++d)
+            if (blocks > 1 + d) {
+                sa[d].template load<MODE>(g.A, g.lda, m0, kb.at(1 + d), g.m, g.k, tid);
+                sb[d].template load<MODE>(g.B, g.ldb, n0, kb.at(1 + d), g.n, g.k, tid);
+            }
         __syncthreads();
-        for (int64_t kt = 0; kt < ktiles; ++kt) {
-            __bf16 *cur = lds + (kt & 1) * STAGE_HALVES;
-            __bf16 *nxt = lds + ((kt + 1) & 1) * STAGE_HALVES;
-            const bool more = kt + 1 < ktiles;
-            if (more) {
-                const int64_t k0 = kb.at(kt + 1);
-                sa.template load<MODE>(g.A, g.lda, m0, k0, g.m, g.k, tid);
-                sb.template load<MODE>(g.B, g.ldb, n0, k0, g.n, g.k, tid);
-            }
-            const __bf16 *As = cur + (wm * SH::WM + l32) * SA::LD + half * 8;
-            const __bf16 *Bs = cur + SA::HALVES + (wn * SH::WN + l32) * SB::LD + half * 8;
+        const int ao = (wm * SH::WM + l32) * SA::LD + half * 8;
+        const int bo = SA::HALVES + (wn * SH::WN + l32) * SB::LD + half * 8;
+        Frags f[2];
+        if (blocks > 0) f[0].read(lds + ao, lds + bo, 0);
+        // Block b of the K loop, in LDS stage b & 1 (given as a constant).
+        auto step = [&](auto whole, int64_t b, int stage) {
+            constexpr bool WHOLE = decltype(whole)::value;
+            const __bf16 *cur = lds + stage * STAGE_HALVES;
+            __bf16 *nxt = lds + (stage ^ 1) * STAGE_HALVES;
+            const int set = SETS == 2 ? stage : 0;
+            const bool store = WHOLE || b + 1 < blocks, load = WHOLE || b + 1 + SETS < blocks;
 #pragma unroll
-            for (int ks = 0; ks < SH::BK / 16; ++ks) {
-                bf16x8 a[SH::RM][3], b[SH::RN][3];
-#pragma unroll
-                for (int i = 0; i < SH::RM; ++i)
-#pragma unroll
-                    for (int t = 0; t < 3; ++t)
-                        a[i][t] = *reinterpret_cast<const bf16x8 *>(
-                            As + t * SA::PART + i * 32 * SA::LD + ks * 16);
-#pragma unroll
-                for (int j = 0; j < SH::RN; ++j)
-#pragma unroll
-                    for (int t = 0; t < 3; ++t)
-                        b[j][t] = *reinterpret_cast<const bf16x8 *>(
-                            Bs + t * SB::PART + j * 32 * SB::LD + ks * 16);
-#pragma unroll
-                for (int i = 0; i < SH::RM; ++i)
-#pragma unroll
-                    for (int j = 0; j < SH::RN; ++j) {
-                        // smallest terms first; (0,0) is the leading product
-                        floatx16 &small = ACC2 ? lo[ACC2 ? i : 0][ACC2 ? j : 0] : acc[i][j];
-                        small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][0], b[j][2], small, 0, 0, 0);
-                        small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][1], b[j][1], small, 0, 0, 0);
-                        small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][2], b[j][0], small, 0, 0, 0);
-                        small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][0], b[j][1], small, 0, 0, 0);
-                        small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][1], b[j][0], small, 0, 0, 0);
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][0], b[j][0], acc[i][j], 0, 0, 0);
+            for (int q = 0; q < NKS; ++q) {
+                if (q + 1 < NKS) {
+                    f[(q + 1) & 1].read(cur + ao, cur + bo, q + 1);
+                } else {
+                    // every wave has stored its part of block b + 1 and has
+                    // read the last of block b
+                    __syncthreads();
+                    if (store) f[0].read(nxt + ao, nxt + bo, 0);
+                }
+                f[q & 1].multiply(acc, lo);
+                if (q == 0) {
+                    if (store) {
+                        sa[set].template store<MODE>(nxt, m0, g.m, tid);
+                        sb[set].template store<MODE>(nxt + SA::HALVES, n0, g.n, tid);
                     }
+                    if (load) {
+                        const int64_t k0 = kb.at(b + 1 + SETS);
+                        sa[set].template load<MODE>(g.A, g.lda, m0, k0, g.m, g.k, tid);
+                        sb[set].template load<MODE>(g.B, g.ldb, n0, k0, g.n, g.k, tid);
+                    }
+                }
+#pragma unroll
+                for (int e = 0; e < 6 * SH::RM * SH::RN; ++e) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // an MFMA
+                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // an LDS read
+                    __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);  // VALU
+                    __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);  // an LDS write
+                    __builtin_amdgcn_sched_group_barrier(0x020, 2, 0);  // loads
+                }
+                __builtin_amdgcn_sched_barrier(0);
             }
-            if (more) {
-                sa.template store<MODE>(nxt, m0, g.m, tid);
-                sb.template store<MODE>(nxt + SA::HALVES, n0, g.n, tid);
+        };
+        int64_t b = 0;
+        if (MODE != MASKED) {
+            for (; b + 2 + SETS < blocks; b += 2) {
+                step(std::true_type{}, b, 0);
+                step(std::true_type{}, b + 1, 1);
             }
-            __syncthreads();
         }
+        for (; b + 1 < blocks; b += 2) {
+            step(std::false_type{}, b, 0);
+            step(std::false_type{}, b + 1, 1);
+        }
+        if (b < blocks) step(std::false_type{}, b, 0);
         if (ACC2) {
 #pragma unroll
             for (int i = 0; i < SH::RM; ++i)
