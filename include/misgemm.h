@@ -376,7 +376,7 @@ typedef struct misgemm_batch misgemm_batch; /* opaque plan */
  * loaded list, so each XCD's L2 serves few problems), order every list by
  * decreasing work (longest first), and upload the problem and tile tables
  * to device memory owned by the plan.
- * config_id < 0 picks the configuration from the tuning table / heuristics;
+ * config_id < 0 picks the configuration from the tuning table / cost model;
  * a tuning-table rule "batch2 <mode> <T> <config> <config2>" instead puts
  * the problems with m >= T and n >= T on <config> and the others on
  * <config2>, as two launches that run concurrently (the second on a stream

@@ -139,9 +139,9 @@ int tuned_config(int mode, int ta, int tb, int64_t m, int64_t n, int64_t k, bool
 // of it.  The five numbers of a row were fitted to the times of every
 // configuration on 95 shapes (64 to 6144 a side, rank-k updates of up to
 // 16384 x 16384, K up to 16384, all transposes; three quarters of them
-// random), the 256-wide FP32 rows and `top` to 8192^3 as well.  Over these the choice is 1.4 % (FP32), 0.7 % (split form) and
-// 0.6 % (split form with a caller's workspace) slower than the fastest
-// configuration of each, at worst 20 %.  The largest tile that gives every
+// random), the 256-wide FP32 rows and `top` to 8192^3 as well.  Over these the choice is 1.4 % (FP32) and 1.5 % (split form,
+// with a caller's workspace too) slower than the fastest configuration of
+// each, at worst 20 %.  The largest tile that gives every
 // CU one, the nearest of the tuned squares before that, and two workgroups
 // per CU by splits chose, in us: 1536x1536x8192 515 for 385, 3000x3000x300
 // 93 for 57, 10144x8795x64 249 for 207, 1511x777x1003 44 for 37.
