@@ -283,8 +283,11 @@ int misgemm_dgemm(char transa, char transb, int64_t m, int64_t n, int64_t k,
  * int64): row ipiv[j] (0-based, >= j) was swapped with row j at step j,
  * first row of largest magnitude on ties.  info (device int): 0, or 1 + the
  * first j with a zero pivot (the factorization then completes without
- * dividing that column, as LAPACK's getrf does).  Recursive right-looking
- * algorithm: the trailing updates and the off-diagonal parts of the
+ * dividing that column, as LAPACK's getrf does), or -1 when the workgroups of
+ * a panel lost each other for more than a second, which nothing but a write
+ * to ipiv from elsewhere during the call can cause; A and ipiv are then not a
+ * factorization.  ipiv holds the workgroups' messages until its entries are
+ * final.  Recursive right-looking algorithm: the trailing updates and the off-diagonal parts of the
  * triangular solves are sgemm calls in `mode` (MISGEMM_FP32 or
  * MISGEMM_BF16X3); panels of 64 columns are factored in one launch each by
  * one or more workgroups, and each panel's interchanges are applied to the
@@ -294,6 +297,19 @@ int misgemm_dgemm(char transa, char transb, int64_t m, int64_t n, int64_t k,
  */
 int misgemm_sgetrf(int64_t n, float *A, int64_t lda, int64_t *ipiv, int *info, int mode,
                    void *stream);
+
+/*
+ * For this library's tests: misgemm_sgetrf with bounds of its own on the start
+ * of a panel of several workgroups.  wait_polls: polls the first workgroup
+ * waits for the others (negative: none, it factors the panel alone, in
+ * memory); word_polls: polls the others wait for its word (0: none, they call
+ * the panel off).  misgemm_sgetrf_waiting takes the second bound of
+ * misgemm_sgetrf.  Arguments and errors otherwise as there.
+ */
+int misgemm_sgetrf_waiting(int64_t n, float *A, int64_t lda, int64_t *ipiv, int *info, int mode,
+                           int wait_polls, void *stream);
+int misgemm_sgetrf_limited(int64_t n, float *A, int64_t lda, int64_t *ipiv, int *info, int mode,
+                           int wait_polls, int word_polls, void *stream);
 
 /*
  * Solve A X = B with the factors of misgemm_sgetrf: B (n x nrhs, device,

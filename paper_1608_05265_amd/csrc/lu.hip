@@ -330,7 +330,9 @@ struct Lu {
     int *info;
     int mode;
     hipStream_t s;
-    int wait_polls;  // of a panel's first workgroup for the others
+    // bounds of a panel's start: the first workgroup's wait for the others and
+    // the others' for its word
+    int wait_polls, word_polls;
 };
 
 int check(hipError_t e) { return e == hipSuccess ? 0 : (int)e; }
@@ -459,10 +461,12 @@ int panel(const Lu &c, float *P, int64_t m, int w, int64_t j0)
     const dim3 grid((unsigned)(groups * stride)), block(PANEL_THREADS);
     if (panel_rpt(m) == 1)
         hipLaunchKernelGGL((lu_panel_kernel<1>), grid, block, 0, c.s, P, c.lda, (int)m, w, c.ipiv,
-                           j0, c.info, words, (int)groups, first, stride, c.wait_polls);
+                           j0, c.info, words, (int)groups, first, stride, c.wait_polls,
+                           c.word_polls);
     else
         hipLaunchKernelGGL((lu_panel_kernel<2>), grid, block, 0, c.s, P, c.lda, (int)m, w, c.ipiv,
-                           j0, c.info, words, (int)groups, first, stride, c.wait_polls);
+                           j0, c.info, words, (int)groups, first, stride, c.wait_polls,
+                           c.word_polls);
     return check(hipGetLastError());
 }
 
@@ -493,11 +497,8 @@ bool lu_mode_ok(int mode) { return mode == MISGEMM_FP32 || mode == MISGEMM_BF16X
 
 extern "C" {
 
-// misgemm_sgetrf with the number of polls that a panel's first workgroup
-// waits for the others (negative: it does not wait and factors every panel
-// of several workgroups alone, in memory): the tests' way to that path.
-int misgemm_sgetrf_waiting(int64_t n, float *A, int64_t lda, int64_t *ipiv, int *info, int mode,
-                           int wait_polls, void *stream)
+int misgemm_sgetrf_limited(int64_t n, float *A, int64_t lda, int64_t *ipiv, int *info, int mode,
+                           int wait_polls, int word_polls, void *stream)
 {
     if (n < 0) return -1;
     if (n > 0 && A == nullptr) return -2;
@@ -511,14 +512,20 @@ int misgemm_sgetrf_waiting(int64_t n, float *A, int64_t lda, int64_t *ipiv, int 
                        info);
     int rc = check(hipGetLastError());
     if (rc != 0 || n == 0) return rc;
-    const Lu c{A, lda, n, ipiv, info, mode, s, wait_polls};
+    const Lu c{A, lda, n, ipiv, info, mode, s, wait_polls, word_polls};
     return getrf(c, 0, n);
+}
+
+int misgemm_sgetrf_waiting(int64_t n, float *A, int64_t lda, int64_t *ipiv, int *info, int mode,
+                           int wait_polls, void *stream)
+{
+    return misgemm_sgetrf_limited(n, A, lda, ipiv, info, mode, wait_polls, PANEL_WORD_WAIT, stream);
 }
 
 int misgemm_sgetrf(int64_t n, float *A, int64_t lda, int64_t *ipiv, int *info, int mode,
                    void *stream)
 {
-    return misgemm_sgetrf_waiting(n, A, lda, ipiv, info, mode, PANEL_WAIT, stream);
+    return misgemm_sgetrf_limited(n, A, lda, ipiv, info, mode, PANEL_WAIT, PANEL_WORD_WAIT, stream);
 }
 
 int misgemm_sgetrs(int64_t n, int64_t nrhs, const float *A, int64_t lda, const int64_t *ipiv,
@@ -534,7 +541,7 @@ int misgemm_sgetrs(int64_t n, int64_t nrhs, const float *A, int64_t lda, const i
     if (!lu_mode_ok(mode)) return -8;
     if (n == 0 || nrhs == 0) return 0;
     const Lu c{const_cast<float *>(A), lda, n, const_cast<int64_t *>(ipiv), nullptr, mode,
-               (hipStream_t)stream, 0};
+               (hipStream_t)stream, 0, 0};
     const bool few = nrhs <= TRSV_MAX_RHS;
     int rc = 0;
     if (few && n <= LASWP_LDS_ROWS) {

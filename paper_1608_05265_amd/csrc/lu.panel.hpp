@@ -29,13 +29,17 @@
 // while the rows fit half of its CUs.
 //
 // Waiting.  Every workgroup waits for messages of the others, so all G must
-// be resident at once.  The first column decides it: the first workgroup
-// (dispatched before the others of its launch) waits a bounded time for
-// everybody's first message and publishes either "go" or "stop"; the others
-// wait for its word.  After "go" every workgroup is resident and each wait
-// ends.  After "stop" (other streams' kernels hold the CUs for long, or
-// several factorizations hold each other's up) the first workgroup factors
-// the panel alone, in memory, and the others end.
+// be resident at once.  The first column decides it, once for the launch, in
+// the start word: the first workgroup waits a bounded time for everybody's
+// first message and swaps in "go" or "stop"; the others wait a bounded, longer
+// time for its word and swap in "stop" when it does not come.  The first swap
+// stands and everybody obeys it, so no workgroup leaves a launch that goes
+// on, in whatever order the workgroups were dispatched (the XCDs dispatch
+// independently, and another stream's kernel can hold back the first
+// workgroup alone).  After "go" every workgroup is resident and has posted,
+// and each wait ends.  After "stop" (other streams' kernels hold the CUs for
+// long, or several factorizations hold each other's up) the first workgroup
+// factors the panel alone, in memory, and the others end.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -56,9 +60,11 @@ constexpr int MSG = PANEL + 16;
 constexpr int MSG_MAG = PANEL, MSG_POS = PANEL + 1, MSG_START = PANEL + 3;
 constexpr int64_t MSG_WORDS = 2 * MSG;  // words per workgroup (two slots)
 constexpr int64_t MSG_ALIGN = 16;       // words
-// Polls of the first workgroup before it stops waiting for the others
-// (about 0.4 us each), and a bound that no wait after "go" reaches.
+// Polls (about 0.4 us each) that the first workgroup waits for the others and
+// the others for its word; and a bound that no wait after "go" reaches, so
+// that the kernel ends even when the words are overwritten under it.
 constexpr int PANEL_WAIT = 1 << 16;
+constexpr int PANEL_WORD_WAIT = 1 << 18;
 constexpr int PANEL_HARD_WAIT = 1 << 22;
 
 // v from another lane of the same 16-lane row (DPP control CTRL).
@@ -144,6 +150,22 @@ __device__ inline uint64_t get_word(const uint64_t *p)
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ inline bool tagged(uint64_t word, uint32_t tag) { return (uint32_t)(word >> 32) == tag; }
+
+enum PanelState { PANEL_GO = 1, PANEL_STOP = 2, PANEL_LOST = 3 };
+
+// The launch's one decision: `vote` if nobody decided before, else what
+// stands in the word.  (A swap fails only where the word changed, which it
+// does once in a launch.)
+__device__ inline int decide(uint64_t *word, uint32_t tag, int vote)
+{
+    uint64_t seen = get_word(word);
+    while (!tagged(seen, tag))
+        if (__hip_atomic_compare_exchange_strong(word, &seen, ((uint64_t)tag << 32) | (uint32_t)vote,
+                                                 __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT))
+            return vote;
+    return (int)(uint32_t)seen;
+}
 
 // The panel in memory by one workgroup of NT threads, every column pass
 // walking it: panels taller than PANEL_GROUPS workgroups hold, and those
@@ -261,7 +283,7 @@ template <int RPT>
 __global__ __launch_bounds__(PANEL_THREADS) void lu_panel_kernel(
     float *__restrict__ P, int64_t lda, int m, int w, int64_t *__restrict__ ipiv, int64_t row0,
     int *__restrict__ info, uint64_t *__restrict__ words, int G, int first, int stride,
-    int wait_polls)
+    int wait_polls, int word_polls)
 {
     static_assert(RPT == 1 || RPT == 2, "rows per thread");
     if ((int)blockIdx.x % stride != first) return;
@@ -270,11 +292,11 @@ __global__ __launch_bounds__(PANEL_THREADS) void lu_panel_kernel(
     __shared__ uint2 skey[PANEL_WAVES];  // the wavefronts' candidates
     __shared__ float su[PANEL];          // the pivot row
     __shared__ uint2 swin;               // its candidate; mag 0: see sstate
-    __shared__ int sstate;               // 1 go, 2 stop, 3 a wait reached its hard bound
+    __shared__ int sstate;               // a PanelState
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);  // scalar branches on it
     const int r0 = RPT * (PANEL_THREADS * g + t);
-    if (t == 0) sstate = 1;
+    if (t == 0) sstate = PANEL_GO;
 
     panel_f4 v[RPT][PANEL / 4];
     int pos[RPT];
@@ -367,17 +389,24 @@ __global__ __launch_bounds__(PANEL_THREADS) void lu_panel_kernel(
         if (G > 1 && wave == ((ow + 1) & (PANEL_WAVES - 1))) {
             const uint64_t *slot = words + (int64_t)(q & 1) * G * MSG;
             const uint64_t *mine = slot + (int64_t)(lane < G ? lane : 0) * MSG;
-            const int bound = q == 0 && g == 0 ? wait_polls : PANEL_HARD_WAIT;
             Candidate x{0, 0xFFFFFFFFu};
-            int st = bound < 0 ? 2 : 1;
+            int st = PANEL_GO, bound = PANEL_HARD_WAIT;
+            if (q == 0 && g == 0) {
+                bound = wait_polls;
+                if (bound < 0) st = PANEL_STOP;
+            }
             if (q == 0 && g > 0) {  // the first workgroup's word
-                uint64_t a;
-                int polls = 0;
+                uint64_t a = 0;
 #pragma unroll 1
-                do {
+                for (int polls = 0; polls < word_polls; ++polls) {
                     a = get_word(words + MSG_START);
-                } while (!tagged(a, tag) && ++polls < PANEL_HARD_WAIT);
-                st = tagged(a, tag) ? (int)(uint32_t)a : 3;
+                    if (tagged(a, tag)) break;
+                }
+                st = (int)(uint32_t)a;
+                if (!tagged(a, tag)) {
+                    if (lane == 0) st = decide(words + MSG_START, tag, PANEL_STOP);
+                    st = __builtin_amdgcn_readfirstlane(st);
+                }
             }
             int win;
             if (G <= NEAR) {
@@ -387,7 +416,7 @@ __global__ __launch_bounds__(PANEL_THREADS) void lu_panel_kernel(
                 uint64_t row[NEAR];
                 uint64_t a = 0, b = 0;
 #pragma unroll 1
-                for (int polls = 0; st == 1; ++polls) {
+                for (int polls = 0; st == PANEL_GO; ++polls) {
                     a = get_word(mine + MSG_MAG);
                     b = get_word(mine + MSG_POS);
 #pragma unroll
@@ -399,7 +428,7 @@ __global__ __launch_bounds__(PANEL_THREADS) void lu_panel_kernel(
 #pragma unroll
                     for (int k = 0; k < NEAR; ++k) all = all && tagged(row[k], tag);
                     if (__all(all)) break;
-                    if (polls >= bound) st = bound == PANEL_HARD_WAIT ? 3 : 2;
+                    if (polls >= bound) st = q == 0 && g == 0 ? PANEL_STOP : PANEL_LOST;
                 }
                 if (lane < G) x = Candidate{(uint32_t)a, (uint32_t)b};
                 gb = lanes_best<NEAR>(x, win);
@@ -409,37 +438,39 @@ __global__ __launch_bounds__(PANEL_THREADS) void lu_panel_kernel(
                 rowv = __uint_as_float(r);
             } else {
 #pragma unroll 1
-                for (int polls = 0; st == 1; ++polls) {
+                for (int polls = 0; st == PANEL_GO; ++polls) {
                     const uint64_t a = get_word(mine + MSG_MAG), b = get_word(mine + MSG_POS);
                     if (lane < G) x = Candidate{(uint32_t)a, (uint32_t)b};
                     if (__all(tagged(a, tag) && tagged(b, tag))) break;
-                    if (polls >= bound) st = bound == PANEL_HARD_WAIT ? 3 : 2;
+                    if (polls >= bound) st = q == 0 && g == 0 ? PANEL_STOP : PANEL_LOST;
                 }
                 gb = lanes_best<PANEL_GROUPS>(x, win);
                 const uint64_t *from = slot + (int64_t)win * MSG;
 #pragma unroll 1
-                for (int polls = 0; st == 1; ++polls) {
+                for (int polls = 0; st == PANEL_GO; ++polls) {
                     const uint64_t a = get_word(from + lane);
                     rowv = __uint_as_float((uint32_t)a);
                     if (__all(tagged(a, tag))) break;
-                    if (polls >= PANEL_HARD_WAIT) st = 3;
+                    if (polls >= PANEL_HARD_WAIT) st = q == 0 && g == 0 ? PANEL_STOP : PANEL_LOST;
                 }
             }
-            if (q == 0 && g == 0 && lane == 0) put_word(words + MSG_START, tag, (uint32_t)st);
+            if (q == 0 && g == 0) {
+                if (lane == 0) st = decide(words + MSG_START, tag, st);
+                st = __builtin_amdgcn_readfirstlane(st);
+            }
             su[lane] = pivot_row(rowv);
             if (lane == 0) {
-                if (st != 1) sstate = st;
-                swin = make_uint2(st == 1 ? gb.mag : 0u, gb.pos);
+                if (st != PANEL_GO) sstate = st;
+                swin = make_uint2(st == PANEL_GO ? gb.mag : 0u, gb.pos);
             }
         }
         __syncthreads();
     };
 
     exchange(0, 0, [](int) {});
-    int state = sstate;  // uniform over the launch
     bool noted = false;
 #pragma unroll 1
-    for (int b = 0; b < PANEL / 8 && state == 1; ++b) {
+    for (int b = 0; b < PANEL / 8; ++b) {
         uint32_t taken = 0;  // bit k: the block's column k has multipliers
 #pragma unroll
         for (int jj = 0; jj < 8; ++jj) {
@@ -463,6 +494,8 @@ __global__ __launch_bounds__(PANEL_THREADS) void lu_panel_kernel(
                 for (int i = 0; i < RPT; ++i) lm[i] = l[i] = v[i][jj / 4][jj % 4] * rinv;
                 taken |= 1u << jj;
                 if (__builtin_expect(!(ok && fabsf(piv) >= FLT_MIN && fabsf(piv) < 0x1p126f), 0)) {
+                    // every panel has a candidate: without one there is no column
+                    if (umag == 0) goto left;
                     rinv = 1.0f / piv;
 #pragma unroll
                     for (int i = 0; i < RPT; ++i) {
@@ -544,38 +577,36 @@ __global__ __launch_bounds__(PANEL_THREADS) void lu_panel_kernel(
             v[i][PANEL / 4 - 2] = x0;
             v[i][PANEL / 4 - 1] = x1;
         }
-        if (8 * (b + 1) < w) {
-            exchange(8 * (b + 1), 0, [](int) {});
-            state = sstate;
-        }
+        if (8 * (b + 1) < w) exchange(8 * (b + 1), 0, [](int) {});
     }
-    if (state != 1) {  // stopped at the first column, or a wait reached its hard bound
-        if (state == 2 && g == 0) panel_in_memory<PANEL_THREADS>(P, lda, m, w, ipiv, row0, info);
-        if (state == 3 && t == 0) *info = -1;
+    {  // store the rows: rows that are done, up to their diagonal
+        const bool plain = act[0] && act[RPT - 1] && pos[0] == r0 && pos[RPT - 1] == r0 + RPT - 1;
+        if (RPT == 2 && __all(plain)) {
+#pragma unroll
+            for (int c = 0; c < PANEL; ++c)
+                if (c < w) {
+                    panel_f2u x;
+                    x[0] = v[0][c / 4][c % 4];
+                    x[1] = v[RPT - 1][c / 4][c % 4];
+                    *reinterpret_cast<panel_f2u *>(P + (int64_t)c * lda + r0) = x;
+                }
+        } else {
+#pragma unroll
+            for (int i = 0; i < RPT; ++i)
+                if (r0 + i < m) {
+                    float *pr = P + pos[i];
+                    const int cols = act[i] ? w : pos[i];
+#pragma unroll
+                    for (int c = 0; c < PANEL; ++c)
+                        if (c < cols) pr[(int64_t)c * lda] = v[i][c / 4][c % 4];
+                }
+        }
         return;
     }
-    // store the rows: rows that are done, up to their diagonal
-    const bool plain = act[0] && act[RPT - 1] && pos[0] == r0 && pos[RPT - 1] == r0 + RPT - 1;
-    if (RPT == 2 && __all(plain)) {
-#pragma unroll
-        for (int c = 0; c < PANEL; ++c)
-            if (c < w) {
-                panel_f2u x;
-                x[0] = v[0][c / 4][c % 4];
-                x[1] = v[RPT - 1][c / 4][c % 4];
-                *reinterpret_cast<panel_f2u *>(P + (int64_t)c * lda + r0) = x;
-            }
-    } else {
-#pragma unroll
-        for (int i = 0; i < RPT; ++i)
-            if (r0 + i < m) {
-                float *pr = P + pos[i];
-                const int cols = act[i] ? w : pos[i];
-#pragma unroll
-                for (int c = 0; c < PANEL; ++c)
-                    if (c < cols) pr[(int64_t)c * lda] = v[i][c / 4][c % 4];
-            }
-    }
+left:  // no column was taken (stop), or a wait reached its hard bound and nothing of it is used
+    if (sstate == PANEL_STOP && g == 0)
+        panel_in_memory<PANEL_THREADS>(P, lda, m, w, ipiv, row0, info);
+    if (sstate == PANEL_LOST && t == 0) *info = -1;
 }
 
 }  // namespace
