@@ -154,11 +154,10 @@ __device__ inline bool tagged(uint64_t word, uint32_t tag) { return (uint32_t)(w
 enum PanelState { PANEL_GO = 1, PANEL_STOP = 2, PANEL_LOST = 3 };
 
 // The launch's one decision: `vote` if nobody decided before, else what
-// stands in the word.  (A swap fails only where the word changed, which it
-// does once in a launch.)
-__device__ inline int decide(uint64_t *word, uint32_t tag, int vote)
+// stands in the word, which was `seen` a while ago.  (A swap fails only where
+// the word changed, which it does once in a launch.)
+__device__ inline int decide(uint64_t *word, uint64_t seen, uint32_t tag, int vote)
 {
-    uint64_t seen = get_word(word);
     while (!tagged(seen, tag))
         if (__hip_atomic_compare_exchange_strong(word, &seen, ((uint64_t)tag << 32) | (uint32_t)vote,
                                                  __ATOMIC_RELAXED, __ATOMIC_RELAXED,
@@ -391,20 +390,17 @@ __global__ __launch_bounds__(PANEL_THREADS) void lu_panel_kernel(
             const uint64_t *mine = slot + (int64_t)(lane < G ? lane : 0) * MSG;
             Candidate x{0, 0xFFFFFFFFu};
             int st = PANEL_GO, bound = PANEL_HARD_WAIT;
-            if (q == 0 && g == 0) {
-                bound = wait_polls;
-                if (bound < 0) st = PANEL_STOP;
-            }
-            if (q == 0 && g > 0) {  // the first workgroup's word
-                uint64_t a = 0;
+            uint64_t start = 0;
+            if (q == 0) {
+                start = get_word(words + MSG_START);
+                if (g == 0) {
+                    bound = wait_polls;
+                    if (bound < 0) st = PANEL_STOP;
+                } else {  // the first workgroup's word
 #pragma unroll 1
-                for (int polls = 0; polls < word_polls; ++polls) {
-                    a = get_word(words + MSG_START);
-                    if (tagged(a, tag)) break;
-                }
-                st = (int)(uint32_t)a;
-                if (!tagged(a, tag)) {
-                    if (lane == 0) st = decide(words + MSG_START, tag, PANEL_STOP);
+                    for (int polls = 0; !tagged(start, tag) && polls < word_polls; ++polls)
+                        start = get_word(words + MSG_START);
+                    if (lane == 0) st = decide(words + MSG_START, start, tag, PANEL_STOP);
                     st = __builtin_amdgcn_readfirstlane(st);
                 }
             }
@@ -455,7 +451,7 @@ __global__ __launch_bounds__(PANEL_THREADS) void lu_panel_kernel(
                 }
             }
             if (q == 0 && g == 0) {
-                if (lane == 0) st = decide(words + MSG_START, tag, st);
+                if (lane == 0) st = decide(words + MSG_START, start, tag, st);
                 st = __builtin_amdgcn_readfirstlane(st);
             }
             su[lane] = pivot_row(rowv);
@@ -468,9 +464,10 @@ __global__ __launch_bounds__(PANEL_THREADS) void lu_panel_kernel(
     };
 
     exchange(0, 0, [](int) {});
+    int state = sstate;
     bool noted = false;
 #pragma unroll 1
-    for (int b = 0; b < PANEL / 8; ++b) {
+    for (int b = 0; b < PANEL / 8 && state == PANEL_GO; ++b) {
         uint32_t taken = 0;  // bit k: the block's column k has multipliers
 #pragma unroll
         for (int jj = 0; jj < 8; ++jj) {
@@ -494,8 +491,6 @@ __global__ __launch_bounds__(PANEL_THREADS) void lu_panel_kernel(
                 for (int i = 0; i < RPT; ++i) lm[i] = l[i] = v[i][jj / 4][jj % 4] * rinv;
                 taken |= 1u << jj;
                 if (__builtin_expect(!(ok && fabsf(piv) >= FLT_MIN && fabsf(piv) < 0x1p126f), 0)) {
-                    // every panel has a candidate: without one there is no column
-                    if (umag == 0) goto left;
                     rinv = 1.0f / piv;
 #pragma unroll
                     for (int i = 0; i < RPT; ++i) {
@@ -578,35 +573,38 @@ __global__ __launch_bounds__(PANEL_THREADS) void lu_panel_kernel(
             v[i][PANEL / 4 - 1] = x1;
         }
         if (8 * (b + 1) < w) exchange(8 * (b + 1), 0, [](int) {});
+        state = sstate;  // of this block's exchanges too
     }
-    {  // store the rows: rows that are done, up to their diagonal
-        const bool plain = act[0] && act[RPT - 1] && pos[0] == r0 && pos[RPT - 1] == r0 + RPT - 1;
-        if (RPT == 2 && __all(plain)) {
-#pragma unroll
-            for (int c = 0; c < PANEL; ++c)
-                if (c < w) {
-                    panel_f2u x;
-                    x[0] = v[0][c / 4][c % 4];
-                    x[1] = v[RPT - 1][c / 4][c % 4];
-                    *reinterpret_cast<panel_f2u *>(P + (int64_t)c * lda + r0) = x;
-                }
-        } else {
-#pragma unroll
-            for (int i = 0; i < RPT; ++i)
-                if (r0 + i < m) {
-                    float *pr = P + pos[i];
-                    const int cols = act[i] ? w : pos[i];
-#pragma unroll
-                    for (int c = 0; c < PANEL; ++c)
-                        if (c < cols) pr[(int64_t)c * lda] = v[i][c / 4][c % 4];
-                }
-        }
+    if (state != PANEL_GO) {
+        // called off before the first column, or a wait reached its hard bound
+        // and nothing of the registers is used
+        if (state == PANEL_STOP && g == 0)
+            panel_in_memory<PANEL_THREADS>(P, lda, m, w, ipiv, row0, info);
+        if (state == PANEL_LOST && t == 0) *info = -1;
         return;
     }
-left:  // no column was taken (stop), or a wait reached its hard bound and nothing of it is used
-    if (sstate == PANEL_STOP && g == 0)
-        panel_in_memory<PANEL_THREADS>(P, lda, m, w, ipiv, row0, info);
-    if (sstate == PANEL_LOST && t == 0) *info = -1;
+    // store the rows: rows that are done, up to their diagonal
+    const bool plain = act[0] && act[RPT - 1] && pos[0] == r0 && pos[RPT - 1] == r0 + RPT - 1;
+    if (RPT == 2 && __all(plain)) {
+#pragma unroll
+        for (int c = 0; c < PANEL; ++c)
+            if (c < w) {
+                panel_f2u x;
+                x[0] = v[0][c / 4][c % 4];
+                x[1] = v[RPT - 1][c / 4][c % 4];
+                *reinterpret_cast<panel_f2u *>(P + (int64_t)c * lda + r0) = x;
+            }
+    } else {
+#pragma unroll
+        for (int i = 0; i < RPT; ++i)
+            if (r0 + i < m) {
+                float *pr = P + pos[i];
+                const int cols = act[i] ? w : pos[i];
+#pragma unroll
+                for (int c = 0; c < PANEL; ++c)
+                    if (c < cols) pr[(int64_t)c * lda] = v[i][c / 4][c % 4];
+            }
+    }
 }
 
 }  // namespace
