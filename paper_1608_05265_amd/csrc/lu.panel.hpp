@@ -234,17 +234,27 @@ __device__ void panel_in_memory(float *__restrict__ P, int64_t lda, int64_t m, i
 typedef float panel_f2u __attribute__((ext_vector_type(2), aligned(4)));
 typedef float panel_f4 __attribute__((ext_vector_type(4)));
 
-// v[G] += u[4G .. 4G+3] nl on every lane's own row, for G = G0, G0 + 1 (u: one
-// element per lane): v_mfma_f32_4x4x1, whose 16 blocks of 4 rows x 4 columns
-// all take block G of u (broadcast controls 4, G), so that lane l's result is
-// its row's four columns, each one fused multiply-add, bit for bit fmaf.
-// Four columns in 8 cycles and no broadcast of u through scalar registers:
-// with readlanes and vector FMAs the updates took over half of the time.
+// v[G] += sum over k of u[k][4G .. 4G+3] nl[k] on every lane's own row, for
+// G = G0, G0 + 1 (u[k]: one element per lane): v_mfma_f32_4x4x1, whose 16
+// blocks of 4 rows x 4 columns all take block G of u (broadcast controls 4,
+// G), so that lane l's result is its row's four columns, each one fused
+// multiply-add, bit for bit fmaf.  Four columns in 8 cycles and no broadcast
+// of u through scalar registers: with readlanes and vector FMAs the updates
+// took over half of the time.  The eight products are summed apart and added
+// once: an entry of the last columns is rounded 7 times by block sums, not 56
+// times at its own magnitude.
 template <int G0>
-__device__ __forceinline__ void rank1_8(panel_f4 (&v)[PANEL / 4], float u, float nl)
+__device__ __forceinline__ void rank8(panel_f4 (&v)[PANEL / 4], const float (&u)[8],
+                                      const float (&nl)[8])
 {
-    v[G0] = __builtin_amdgcn_mfma_f32_4x4x1f32(u, nl, v[G0], 4, G0, 0);
-    v[G0 + 1] = __builtin_amdgcn_mfma_f32_4x4x1f32(u, nl, v[G0 + 1], 4, G0 + 1, 0);
+    panel_f4 s0 = {0.0f, 0.0f, 0.0f, 0.0f}, s1 = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        s0 = __builtin_amdgcn_mfma_f32_4x4x1f32(u[k], nl[k], s0, 4, G0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_4x4x1f32(u[k], nl[k], s1, 4, G0 + 1, 0);
+    }
+    v[G0] += s0;
+    v[G0 + 1] += s1;
 }
 
 // Factor the m x w panel P (w <= PANEL, leading dimension lda; its top-left
@@ -276,8 +286,8 @@ __device__ __forceinline__ void rank1_8(panel_f4 (&v)[PANEL / 4], float u, float
 // takes its 8 cycles however few lanes are active.)  Another wavefront (the
 // poster would wait for its own stores first) reads all candidates, takes the
 // winner's row and, in the columns after the block, applies the block's
-// earlier pivot rows to it with the row's own multipliers, in order: the
-// next pivot row.
+// earlier pivot rows to it with the row's own multipliers, summed in order
+// and added once: the next pivot row.
 template <int RPT>
 __global__ __launch_bounds__(PANEL_THREADS) void lu_panel_kernel(
     float *__restrict__ P, int64_t lda, int m, int w, int64_t *__restrict__ ipiv, int64_t row0,
@@ -350,10 +360,10 @@ __global__ __launch_bounds__(PANEL_THREADS) void lu_panel_kernel(
         // the pivot row from a candidate row: in the columns after the block,
         // the block's earlier pivot rows with the row's own multipliers
         const auto pivot_row = [&](float r) __attribute__((always_inline)) {
-            float x = r;
+            float s = 0.0f;
 #pragma unroll
-            for (int k = 0; k < col; ++k) x = fmaf(-lane_value(r, k), ub[k], x);
-            return lane < 8 ? r : x;
+            for (int k = 0; k < col; ++k) s = fmaf(-lane_value(r, k), ub[k], s);
+            return lane < 8 ? r : r + s;
         };
         if (wave == ow) {
             if (gb.mag != 0) {
@@ -481,9 +491,11 @@ __global__ __launch_bounds__(PANEL_THREADS) void lu_panel_kernel(
                 const int p = __builtin_amdgcn_readfirstlane((int)winner.y);
                 const float piv = lane_value(u, jj), urow = u;
                 const bool ok = umag > MAG_ZERO;
-                // multipliers: by the reciprocal to half an ulp (and 2^-24 of
-                // one), the hardware's and one Newton step; lm: as the updates
-                // of this column take them
+                // multipliers, by the rounded reciprocal: the hardware's, an ulp
+                // off at most, and one Newton step give what 1.0f / piv does
+                // for every significand (all 2^23 compared, at exponents from
+                // the least to the largest taken here); lm: as the updates of
+                // this column take them
                 float l[RPT], lm[RPT];
                 float rinv = __builtin_amdgcn_rcpf(piv);
                 rinv = fmaf(fmaf(-piv, rinv, 1.0f), rinv, rinv);
@@ -549,19 +561,13 @@ __global__ __launch_bounds__(PANEL_THREADS) void lu_panel_kernel(
                 nl[i][k] = (taken >> k) & 1 ? -v[i][k / 4][k % 4] : 0.0f;
 #pragma unroll
         for (int i = 0; i < RPT; ++i) {
-#define MISGEMM_RANK8(GROUP)                                                    \
-    if (b < 8 - GROUP / 2) {                                                    \
-        _Pragma("unroll") for (int k = 0; k < 8; ++k)                           \
-            rank1_8<GROUP>(v[i], ub[k], nl[i][k]);                              \
-    }
-            MISGEMM_RANK8(2)
-            MISGEMM_RANK8(4)
-            MISGEMM_RANK8(6)
-            MISGEMM_RANK8(8)
-            MISGEMM_RANK8(10)
-            MISGEMM_RANK8(12)
-            MISGEMM_RANK8(14)
-#undef MISGEMM_RANK8
+            if (b < 7) rank8<2>(v[i], ub, nl[i]);
+            if (b < 6) rank8<4>(v[i], ub, nl[i]);
+            if (b < 5) rank8<6>(v[i], ub, nl[i]);
+            if (b < 4) rank8<8>(v[i], ub, nl[i]);
+            if (b < 3) rank8<10>(v[i], ub, nl[i]);
+            if (b < 2) rank8<12>(v[i], ub, nl[i]);
+            if (b < 1) rank8<14>(v[i], ub, nl[i]);
         }
         // rotate the registers by the block's eight columns
 #pragma unroll

@@ -90,3 +90,88 @@ def test_factorization_beside_a_product_that_fills_the_card():
     for _ in range(3):
         mg.sgemm("N", "N", k, k, k, 1.0, B, k, B, k, 0.0, C, k, stream=side)
     _check(Factors(a).get(), want, n)
+
+
+def _fma(a, b, c):
+    """a * b + c in float32, rounded once: exact product, the sum rounded to
+    odd in double (its last bit set where it is not exact), then to float."""
+    p = a.astype(np.float64) * b.astype(np.float64)
+    c = np.broadcast_to(c, p.shape).astype(np.float64)
+    t = p + c
+    bv = t - p
+    err = (p - (t - bv)) + (c - bv)
+    bits = t.view(np.int64)
+    toward = np.where((err > 0) == (t > 0), 1, -1)  # away from zero or towards it
+    bits = np.where((err != 0) & (bits & 1 == 0), bits + toward, bits)
+    return bits.view(np.float64).astype(np.float32)
+
+
+def _panel(a):
+    """The factored panel and its pivots, in float32: columns in blocks of
+    eight, a pivot row subtracted at once from the block's own columns and the
+    block's eight together, summed apart in order, from the later ones."""
+    a = a.copy()
+    m, w = a.shape
+    piv = np.empty(w, np.int64)
+    for b in range(0, w, 8):
+        e = min(b + 8, w)
+        for j in range(b, e):
+            p = j + int(np.argmax(np.abs(a[j:, j])))
+            piv[j] = p
+            a[[j, p]] = a[[p, j]]
+            a[j + 1:, j] *= np.float32(1) / a[j, j]
+            a[j + 1:, j + 1:e] = _fma(-a[j + 1:, j, None], a[None, j, j + 1:e], a[j + 1:, j + 1:e])
+        for r in range(b + 1, e):
+            s = np.zeros(w - e, np.float32)
+            for k in range(b, r):
+                s = _fma(-a[r, k, None], a[k, e:], s)
+            a[r, e:] += s
+        s = np.zeros((m - e, w - e), np.float32)
+        for k in range(b, e):
+            s = _fma(-a[e:, k, None], a[None, k, e:], s)
+        a[e:, e:] += s
+    return a, piv
+
+
+@pytest.mark.parametrize("n", [5, 50, 64, 200, 600, 1100, 2600])
+def test_first_panel_bit_for_bit(n):
+    """One workgroup with one and two rows per thread, several workgroups,
+    whole and partial blocks, against the same sums in numpy."""
+    a = np.random.default_rng(68).uniform(-1, 1, (n, n)).astype(np.float32)
+    w = min(n, 64)
+    want, piv = _panel(a[:, :w])
+    lu, ipiv, info = Factors(a).get()
+    for j in range(w, n):  # the later panels' interchanges
+        want[[j, ipiv[j]]] = want[[ipiv[j], j]]
+    assert info == 0 and np.array_equal(ipiv[:w], piv)
+    assert np.array_equal(lu[:, :w], want)
+
+
+# significands after which a Newton step from a reciprocal an ulp off would
+# round the wrong way
+HARD_PIVOTS = [0x069913, 0x07cc45, 0x0efa43, 0x109909, 0x186799, 0x1beaaf, 0x20ddd1, 0x224cf7,
+               0x26449f, 0x2aaaac, 0x2b8be1, 0x2d1367, 0x384a93, 0x423dc3, 0x50ac19, 0x50dd0d,
+               0x525d25, 0x543d43, 0x5c23dd, 0x5e86a9, 0x605475, 0x61368b, 0x625473, 0x6c7ec7,
+               0x6e4bc5, 0x700ff1, 0x702a3b, 0x70ff0f, 0x7c3237, 0x7e01ff, 0x7ffffd, 0x7fffff]
+
+
+def test_multipliers_are_the_entries_times_the_rounded_reciprocal():
+    """A lower triangular matrix whose diagonal holds the pivots: nothing is
+    updated, so L is each column times its pivot's reciprocal, rounded twice
+    (divided by a subnormal pivot), bit for bit."""
+    rng = np.random.default_rng(67)
+    n = 700
+    piv = (0x3f800000 | rng.integers(0, 1 << 23, n)).astype(np.uint32)
+    piv[:32] = np.uint32(0x3f800000) | np.array(HARD_PIVOTS, np.uint32)
+    piv = piv.view(np.float32) * np.exp2(rng.integers(-100, 100, n)).astype(np.float32)
+    piv[40], piv[41], piv[42] = 2.0 ** -140, 1.5 * 2.0 ** 126, np.finfo(np.float32).max
+    piv[50::2] *= -1
+    a = np.tril(rng.uniform(-0.99, 0.99, (n, n)).astype(np.float32), -1) * np.abs(piv)
+    a[np.arange(n), np.arange(n)] = piv
+    with np.errstate(over="ignore", invalid="ignore"):
+        want = np.where(np.abs(piv) >= np.float32(2.0 ** -126), a * (np.float32(1) / piv), a / piv)
+    want = np.tril(want.astype(np.float32), -1)
+    want[np.arange(n), np.arange(n)] = piv
+    lu, ipiv, info = Factors(a).get()
+    assert info == 0 and np.array_equal(ipiv, np.arange(n))
+    assert np.array_equal(lu, want)
