@@ -168,64 +168,105 @@ __device__ inline int decide(uint64_t *word, uint64_t seen, uint32_t tag, int vo
 
 // The panel in memory by one workgroup of NT threads, every column pass
 // walking it: panels taller than PANEL_GROUPS workgroups hold, and those
-// whose workgroups did not come together.  w <= PANEL.
+// whose workgroups did not come together.  w <= PANEL.  The same operations in
+// the same order as lu_panel_kernel's (columns in blocks of eight, a block's
+// products summed apart), so that the factors do not depend on which of the
+// two a panel took.
 template <int NT>
 __device__ void panel_in_memory(float *__restrict__ P, int64_t lda, int64_t m, int w,
                                 int64_t *__restrict__ ipiv, int64_t row0, int *__restrict__ info)
 {
     __shared__ float sbest[NT];
     __shared__ int64_t sidx[NT];
-    __shared__ float urow[PANEL];
+    __shared__ float su[8][PANEL];  // the block's pivot rows in the columns after it
     const int t = threadIdx.x;
-    for (int j = 0; j < w; ++j) {
-        float *col = P + (int64_t)j * lda;
-        float best = -1.0f;
-        int64_t idx = -1;
-        for (int64_t r = j + t; r < m; r += NT) {
-            const float v = fabsf(col[r]);
-            if (v > best) { best = v; idx = r; }
-        }
-        sbest[t] = best;
-        sidx[t] = idx;
-        __syncthreads();
-        for (int s = NT / 2; s > 0; s >>= 1) {
-            if (t < s) {
-                const float b1 = sbest[t + s];
-                const int64_t i1 = sidx[t + s];
-                if (i1 >= 0 && (sidx[t] < 0 || b1 > sbest[t] || (b1 == sbest[t] && i1 < sidx[t]))) {
-                    sbest[t] = b1;
-                    sidx[t] = i1;
+    for (int b = 0; b < w; b += 8) {
+        const int e = b + 8 < w ? b + 8 : w;
+        uint32_t taken = 0;  // bit k: column b + k has multipliers
+        for (int j = b; j < e; ++j) {
+            float *col = P + (int64_t)j * lda;
+            float best = -1.0f;
+            int64_t idx = -1;
+            for (int64_t r = j + t; r < m; r += NT) {
+                const float v = fabsf(col[r]);
+                if (v > best) { best = v; idx = r; }
+            }
+            sbest[t] = best;
+            sidx[t] = idx;
+            __syncthreads();
+            for (int s = NT / 2; s > 0; s >>= 1) {
+                if (t < s) {
+                    const float b1 = sbest[t + s];
+                    const int64_t i1 = sidx[t + s];
+                    if (i1 >= 0 && (sidx[t] < 0 || b1 > sbest[t] || (b1 == sbest[t] && i1 < sidx[t]))) {
+                        sbest[t] = b1;
+                        sidx[t] = i1;
+                    }
                 }
+                __syncthreads();
+            }
+            const int64_t p = sidx[0] >= 0 ? sidx[0] : j;
+            const float pivot_mag = sbest[0];
+            __syncthreads();
+            if (t == 0) ipiv[row0 + j] = row0 + p;
+            if (p != j && t < w) {
+                float *c = P + (int64_t)t * lda;
+                const float x = c[j];
+                c[j] = c[p];
+                c[p] = x;
+            }
+            __syncthreads();
+            const float piv = col[j];
+            if (pivot_mag > 0.0f && piv != 0.0f) {
+                if (scale_by_reciprocal(piv)) {
+                    const float rinv = 1.0f / piv;
+                    for (int64_t r = j + 1 + t; r < m; r += NT) col[r] = col[r] * rinv;
+                } else {
+                    for (int64_t r = j + 1 + t; r < m; r += NT) col[r] = col[r] / piv;
+                }
+                taken |= 1u << (j - b);
+                if (t > j && t < e) su[0][t] = P[j + (int64_t)t * lda];
+                __syncthreads();
+                for (int64_t r = j + 1 + t; r < m; r += NT) {
+                    const float l = col[r];
+                    for (int c = j + 1; c < e; ++c) {
+                        float *x = P + r + (int64_t)c * lda;
+                        *x = fmaf(-l, su[0][c], *x);
+                    }
+                }
+            } else if (t == 0 && *info == 0) {
+                *info = (int)(row0 + j + 1);
             }
             __syncthreads();
         }
-        const int64_t p = sidx[0] >= 0 ? sidx[0] : j;
-        const float pivot_mag = sbest[0];
-        __syncthreads();
-        if (t == 0) ipiv[row0 + j] = row0 + p;
-        if (p != j && t < w) {
-            float *c = P + (int64_t)t * lda;
-            const float x = c[j];
-            c[j] = c[p];
-            c[p] = x;
+        if (e == w) break;
+        // the pivot rows in the later columns, a column per thread
+        if (t < w - e) {
+            float *c = P + b + (int64_t)(e + t) * lda;
+            float x[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                float s = 0.0f;
+#pragma unroll
+                for (int k = 0; k < i; ++k)
+                    if ((taken >> k) & 1) s = fmaf(-P[b + i + (int64_t)(b + k) * lda], x[k], s);
+                x[i] = c[i] + s;
+                c[i] = x[i];
+                su[i][t] = (taken >> i) & 1 ? x[i] : 0.0f;
+            }
         }
         __syncthreads();
-        const float piv = col[j];
-        if (pivot_mag > 0.0f && piv != 0.0f) {
-            if (scale_by_reciprocal(piv)) {
-                const float rinv = 1.0f / piv;
-                for (int64_t r = j + 1 + t; r < m; r += NT) col[r] = col[r] * rinv;
-            } else {
-                for (int64_t r = j + 1 + t; r < m; r += NT) col[r] = col[r] / piv;
+        for (int64_t r = e + t; r < m; r += NT) {
+            float nl[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                nl[k] = (taken >> k) & 1 ? -P[r + (int64_t)(b + k) * lda] : -0.0f;
+            for (int c = e; c < w; ++c) {
+                float s = 0.0f;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) s = fmaf(su[k][c - e], nl[k], s);
+                P[r + (int64_t)c * lda] += s;
             }
-            if (t > j && t < w) urow[t] = P[j + (int64_t)t * lda];
-            __syncthreads();
-            for (int64_t r = j + 1 + t; r < m; r += NT) {
-                const float l = col[r];
-                for (int c = j + 1; c < w; ++c) P[r + (int64_t)c * lda] -= l * urow[c];
-            }
-        } else if (t == 0 && *info == 0) {
-            *info = (int)(row0 + j + 1);
         }
         __syncthreads();
     }
@@ -330,6 +371,7 @@ __global__ __launch_bounds__(PANEL_THREADS) void lu_panel_kernel(
     }
 
     float ub[8];  // the block's pivot rows, lane c: register column c
+    uint32_t taken = 0;  // bit k: the block's column k has multipliers
 
     // Post the best candidate of panel column q, which is register column
     // `col`, and learn the winner: swin and su (the pivot row).  aside(ow),
@@ -358,11 +400,13 @@ __global__ __launch_bounds__(PANEL_THREADS) void lu_panel_kernel(
         const uint32_t tag = (uint32_t)(row0 + q + 1);
         float rowv = 0.0f;
         // the pivot row from a candidate row: in the columns after the block,
-        // the block's earlier pivot rows with the row's own multipliers
+        // the block's earlier pivot rows with the row's own multipliers (the
+        // entries of a column without a pivot, NaN perhaps, are none)
         const auto pivot_row = [&](float r) __attribute__((always_inline)) {
+            const float l = __builtin_amdgcn_inverse_ballot_w64(taken | ~0xFFull) ? r : 0.0f;
             float s = 0.0f;
 #pragma unroll
-            for (int k = 0; k < col; ++k) s = fmaf(-lane_value(r, k), ub[k], s);
+            for (int k = 0; k < col; ++k) s = fmaf(-lane_value(l, k), ub[k], s);
             return lane < 8 ? r : r + s;
         };
         if (wave == ow) {
@@ -478,7 +522,7 @@ __global__ __launch_bounds__(PANEL_THREADS) void lu_panel_kernel(
     bool noted = false;
 #pragma unroll 1
     for (int b = 0; b < PANEL / 8 && state == PANEL_GO; ++b) {
-        uint32_t taken = 0;  // bit k: the block's column k has multipliers
+        taken = 0;
 #pragma unroll
         for (int jj = 0; jj < 8; ++jj) {
             const int j = 8 * b + jj;
@@ -558,7 +602,7 @@ __global__ __launch_bounds__(PANEL_THREADS) void lu_panel_kernel(
         for (int i = 0; i < RPT; ++i)
 #pragma unroll
             for (int k = 0; k < 8; ++k)
-                nl[i][k] = (taken >> k) & 1 ? -v[i][k / 4][k % 4] : 0.0f;
+                nl[i][k] = (taken >> k) & 1 ? -v[i][k / 4][k % 4] : -0.0f;
 #pragma unroll
         for (int i = 0; i < RPT; ++i) {
             if (b < 7) rank8<2>(v[i], ub, nl[i]);

@@ -25,14 +25,16 @@ def _limited():
 class Factors:
     """The factorization of a (queued on `stream`, not waited for)."""
 
-    def __init__(self, a, stream=None, wait_polls=PANEL_WAIT, word_polls=WORD_WAIT):
+    def __init__(self, a, stream=None, wait_polls=PANEL_WAIT, word_polls=WORD_WAIT, sync=True):
         import torch
         n = a.shape[0]
         self.A = torch.from_numpy(np.ascontiguousarray(a.T)).to("cuda:0")
         self.piv = torch.empty(n, dtype=torch.int64, device="cuda:0")
         self.inf = torch.empty(1, dtype=torch.int32, device="cuda:0")
-        torch.cuda.synchronize()
         s = stream or torch.cuda.current_stream()
+        s.wait_stream(torch.cuda.current_stream())  # the copy
+        if sync:
+            torch.cuda.synchronize()
         rc = _limited()(n, self.A.data_ptr(), n, self.piv.data_ptr(), self.inf.data_ptr(), 0,
                         wait_polls, word_polls, s.cuda_stream)
         assert rc == 0
@@ -175,3 +177,70 @@ def test_multipliers_are_the_entries_times_the_rounded_reciprocal():
     lu, ipiv, info = Factors(a).get()
     assert info == 0 and np.array_equal(ipiv, np.arange(n))
     assert np.array_equal(lu, want)
+
+
+@pytest.mark.parametrize("kind", ["uniform", "ties", "scaled", "subnormal", "huge", "nan"])
+@pytest.mark.parametrize("n", [600, 1100, 2500])
+def test_bits_do_not_depend_on_whether_the_workgroups_met(n, kind):
+    """Panels called off by the first workgroup or by the others, factored in
+    memory, give the same factors as those that go on, bit for bit."""
+    rng = np.random.default_rng(69)
+    a = rng.uniform(-1, 1, (n, n))
+    if kind == "ties":
+        a = rng.integers(-2, 3, (n, n))
+        a[:, 3] = a[:, 70] = 0
+    elif kind == "scaled":
+        a = a * np.exp2(rng.integers(-60, 60, (n, n)))
+    elif kind == "subnormal":
+        a = a * 2.0 ** -130
+    elif kind == "huge":
+        a = a * 2.0 ** 126
+    elif kind == "nan":
+        a[:, 3], a[:, 20], a[5, 21], a[7, 22] = 0, np.nan, np.inf, np.nan
+    a = a.astype(np.float32)
+    lu, ipiv, info = Factors(a).get()
+    for limits in (dict(wait_polls=-1), dict(word_polls=0)):
+        lu2, ipiv2, info2 = Factors(a, **limits).get()
+        assert info == info2 and np.array_equal(ipiv, ipiv2), limits
+        assert np.array_equal(lu, lu2, equal_nan=True), limits
+
+
+def test_bits_do_not_depend_on_what_else_runs():
+    """Six factorizations on streams of their own beside products that fill
+    the card, against each alone; panels over one XCD (n = 1600) and over all
+    of them (16500)."""
+    import torch
+    import paper_1608_05265_amd as mg
+    rng = np.random.default_rng(70)
+    big = torch.empty(8192 * 8192, device="cuda:0").uniform_(-1, 1)
+    out = torch.empty_like(big)
+    for n, count in ((1600, 6), (16500, 1)):
+        mats = [rng.random((n, n), np.float32) - np.float32(0.5) for _ in range(count)]
+        alone = []
+        for a in mats:
+            f = Factors(a)
+            torch.cuda.synchronize()
+            alone.append((f.A, f.piv))
+        side = torch.cuda.Stream()
+        streams = [torch.cuda.Stream() for _ in mats]
+        for _ in range(2):
+            mg.sgemm("N", "N", 8192, 8192, 8192, 1.0, big, 8192, big, 8192, 0.0, out, 8192, stream=side)
+        runs = [Factors(a, s, sync=False) for a, s in zip(mats, streams)]
+        torch.cuda.synchronize()
+        for (A, piv), r in zip(alone, runs):
+            assert torch.equal(A, r.A) and torch.equal(piv, r.piv) and int(r.inf.item()) == 0, n
+
+
+def test_a_column_of_nan_stays_out_of_the_panel():
+    """A column with no pivot has no multipliers: NaN in it reaches no other
+    column of its panel, whichever way that is factored."""
+    rng = np.random.default_rng(71)
+    a = rng.uniform(-1, 1, (64, 64)).astype(np.float32)
+    b = a.copy()
+    for col in (0, 5, 18):
+        a[:, col], b[:, col] = 0, np.nan
+    lu, ipiv, info = Factors(a).get()
+    lu2, ipiv2, info2 = Factors(b).get()
+    assert info == info2 == 1 and np.array_equal(ipiv, ipiv2)
+    keep = [c for c in range(64) if c not in (0, 5, 18)]
+    assert np.array_equal(lu[:, keep], lu2[:, keep])
