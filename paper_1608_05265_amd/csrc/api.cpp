@@ -205,13 +205,18 @@ const std::vector<ModelConfig> &model_configs(int mode)
     return all[mode];
 }
 
+// A launch holds less than 2^32 threads in a dimension of its grid.
+bool grid_fits(double workgroups, int threads) { return workgroups * threads <= UINT32_MAX; }
+
 // allow_split: whether partial sums have a place to go.  splits: 1 for whole K.
+// A configuration whose launch would be too large (small tiles on a few rows
+// by 2^27 columns) counts as slower than any that fits.
 int model_config(int mode, int64_t m, int64_t n, int64_t k, int cus, bool allow_packed,
                  bool allow_split, int *splits)
 {
     const auto &table = configs();
     int best = -1;
-    double best_us = 1e300;
+    double best_us = INFINITY;
     *splits = 1;
     for (const ModelConfig &mc : model_configs(mode)) {
         if (mc.id < 0) continue;
@@ -239,6 +244,7 @@ int model_config(int mode, int64_t m, int64_t n, int64_t k, int cus, bool allow_
                 us += sc.launch + s * tiles * area * 8.0 / (sc.rate * 1e6) + sc.add * s * area / 4096.0;
             }
             us = fmax(us, least);
+            if (!grid_fits(tiles * s, d.threads)) us = 1e200 * (tiles * s * d.threads);
             if (us < best_us) {
                 best_us = us;
                 best = mc.id;
@@ -550,7 +556,7 @@ int run_sgemm(char transa, char transb, int64_t m, int64_t n, int64_t k, float a
     const ConfigEntry &e = table[cfg];
     const misgemm_config_desc &d = e.desc;
     const int64_t tiles = ((m + d.bm - 1) / d.bm) * ((n + d.bn - 1) / d.bn);
-    if (tiles > INT32_MAX) return MISGEMM_E_TOO_LARGE;
+    if (tiles > INT32_MAX || !grid_fits((double)tiles, d.threads)) return MISGEMM_E_TOO_LARGE;
     GemmArgs g = make_args(m, n, k, alpha, A, lda, B, ldb, beta, C, ldc);
     if (d.packed) return (int)launch_packed_path(e, ta, tb, g, ws, gm, s);
     const bool forced = splits_req >= 1;
@@ -558,6 +564,7 @@ int run_sgemm(char transa, char transb, int64_t m, int64_t n, int64_t k, float a
     splits = effective_splits(k, d.bk, splits);
     if (splits > 1) {
         if (e.splitk[0][0] == nullptr) return MISGEMM_E_BAD_CONFIG;
+        if (!grid_fits((double)tiles * splits, d.threads)) return MISGEMM_E_TOO_LARGE;
         const int64_t need = (int64_t)splits * tiles * d.bm * d.bn * 4;
         void *part = nullptr;
         int wrc = 0;

@@ -12,6 +12,9 @@
 #include "dgemm.hpp"
 #include "registry.hpp"
 
+#include <math.h>
+
+#include <algorithm>
 #include <type_traits>
 
 namespace misgemm {
@@ -336,6 +339,10 @@ hipError_t launch_dgemm_shape(int ta, int tb, const DArgs &g, hipStream_t s)
 //   512x512x2048      32x32 27.9   in four groups 24.0   16x16 29.5
 //   256x256x4096      64x64 122    32x32 in four groups 39.9   16x16 21.9
 //   64x64x4096        64x64 122    32x32 in four groups 38.6   16x16 15.8
+// A launch holds less than 2^32 threads: a tile shape that would need more
+// (16x16 on 16 rows by 2^27 columns) is left out, and a call too large for
+// 64x64 tiles is cut along its longer side, up to the size that 128x128 tiles
+// of 256 threads could take.
 hipError_t launch_dgemm_fp64(int ta, int tb, int64_t m, int64_t n, int64_t k, double alpha,
                              const double *A, int64_t lda, const double *B, int64_t ldb,
                              double beta, double *C, int64_t ldc, int cus, hipStream_t s)
@@ -345,12 +352,28 @@ hipError_t launch_dgemm_fp64(int ta, int tb, int64_t m, int64_t n, int64_t k, do
     g.A = A; g.B = B; g.C = C;
     g.lda = lda; g.ldb = ldb; g.ldc = ldc;
     g.alpha = alpha; g.beta = beta;
-    auto cost = [&](int edge, double share) {
-        const int64_t tiles = ((m + edge - 1) / edge) * ((n + edge - 1) / edge);
-        return (double)((tiles + cus - 1) / cus) * edge * edge / share;
+    auto tiles = [&](int64_t edge) { return ((m + edge - 1) / edge) * ((n + edge - 1) / edge); };
+    if ((double)tiles(128) * 256 > UINT32_MAX) return hipErrorInvalidConfiguration;
+    if (tiles(64) * 256 > UINT32_MAX) {
+        const int64_t half = (std::max(m, n) / 2 + 63) / 64 * 64;
+        const bool rows = m > n;
+        const hipError_t e = launch_dgemm_fp64(ta, tb, rows ? half : m, rows ? n : half, k, alpha, A,
+                                               lda, B, ldb, beta, C, ldc, cus, s);
+        if (e != hipSuccess) return e;
+        if (rows)
+            return launch_dgemm_fp64(ta, tb, m - half, n, k, alpha, A + (ta ? half * lda : half), lda,
+                                     B, ldb, beta, C + half, ldc, cus, s);
+        return launch_dgemm_fp64(ta, tb, m, n - half, k, alpha, A, lda, B + (tb ? half : half * ldb),
+                                 ldb, beta, C + half * ldc, ldc, cus, s);
+    }
+    auto cost = [&](int edge, int threads, double share) {
+        const int64_t t = tiles(edge);
+        return t * threads > UINT32_MAX ? INFINITY
+                                        : (double)((t + cus - 1) / cus) * edge * edge / share;
     };
-    const bool alone = ((m + 31) / 32) * ((n + 31) / 32) <= cus;  // a 32x32 tile per CU
-    const double c64 = cost(64, 0.9), mid = cost(32, alone ? 0.7 : 0.78), c16 = cost(16, 0.4);
+    const bool alone = tiles(32) <= cus;  // a 32x32 tile per CU
+    const double c64 = cost(64, 256, 0.9), mid = cost(32, 256, alone ? 0.7 : 0.78),
+                 c16 = cost(16, 512, 0.4);
     if (c16 < mid && c16 < c64) return launch_dgemm_shape<DShape<16, 16, 64, 16, 16, 8, 2>>(ta, tb, g, s);
     if (c64 <= mid) return launch_dgemm_shape<DShape<64, 64, 16, 32, 32, 1, 2>>(ta, tb, g, s);
     if (alone) return launch_dgemm_shape<DShape<32, 32, 64, 32, 16, 4, 2>>(ta, tb, g, s);

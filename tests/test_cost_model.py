@@ -36,3 +36,15 @@ def test_tile_follows_the_size(mode, large, small):
         assert area(s, s, s) <= small
     for s in (900, 1000, 1024):
         assert small < area(s, s, 2048) < large or area(s, s, 2048) == 64 * 64
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+def test_choice_fits_a_launch(mode):
+    """A launch holds less than 2^32 threads: thin and very wide problems take
+    a tile whose launch does."""
+    cfgs = {c["id"]: c for c in mg.configs(mode)}
+    for m, n, k in ((1, 1 << 27, 16), (16, 1 << 27, 16), (1, 1 << 28, 64), (1 << 28, 1, 64),
+                    (32, 1 << 29, 8), (1 << 29, 1, 300), (1, (1 << 31) - 1024, 1)):
+        c = cfgs[mg.select_config("N", "N", m, n, k, mode)]
+        tiles = -(-m // c["bm"]) * -(-n // c["bn"])
+        assert tiles * c["threads"] < 1 << 32, (m, n, k, c["name"])
