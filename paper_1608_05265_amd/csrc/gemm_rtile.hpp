@@ -22,9 +22,9 @@
 //           from lane group g.
 //   BF16X3: v_mfma_f32_16x16x32_bf16 step t (0 .. KPL/8 - 1) takes the eight
 //           k = c0 + KPL g + 8t .. +7 from lane group g; each FP32 element is
-//           split into three bf16 parts in registers and the six part
-//           products of a step are added smallest first into the one FP32
-//           accumulator, as in the staged split-form tiles.
+//           split into three bf16 parts in registers; the leading part
+//           product of a step goes into one FP32 accumulator, the five small
+//           ones, smallest first, into another.
 // The accumulator of a block gives lane l rows 4*(l/16) .. 4*(l/16)+3 of
 // column l % 16.
 #pragma once
@@ -252,8 +252,9 @@ struct RMathF32 {
     }
 };
 
+// Two chains here too: the leading products and the five small ones.
 struct RMathX3 {
-    static constexpr int CHAINS = 1;
+    static constexpr int CHAINS = 2;
     template <int RM, int RN, int KPL>
     __device__ __forceinline__ static void step(const float (&a)[RM][KPL],
                                                 const float (&b)[RN][KPL],
@@ -286,13 +287,14 @@ struct RMathX3 {
             for (int i = 0; i < RM; ++i)
 #pragma unroll
                 for (int j = 0; j < RN; ++j) {
-                    floatx4 &c = acc[0][i][j];
+                    floatx4 &c = acc[1][i][j];
                     c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap[i][0], bp[j][2], c, 0, 0, 0);
                     c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap[i][1], bp[j][1], c, 0, 0, 0);
                     c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap[i][2], bp[j][0], c, 0, 0, 0);
                     c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap[i][0], bp[j][1], c, 0, 0, 0);
                     c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap[i][1], bp[j][0], c, 0, 0, 0);
-                    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap[i][0], bp[j][0], c, 0, 0, 0);
+                    acc[0][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap[i][0], bp[j][0],
+                                                                          acc[0][i][j], 0, 0, 0);
                 }
         }
     }
