@@ -77,7 +77,7 @@ void register_x3(std::vector<ConfigEntry> &out)
     out.push_back(make_x3<X3Q13, Shape<128, 128, 16, 64, 64>, true, true>("x3q_128x128x16_w64x64"));
     out.push_back(make_x3<X3S, Shape<128, 128, 32, 64, 64>, true>("x3_128x128x32_w64x64"));
     out.push_back(make_x3<X3D, Shape<128, 128, 32, 64, 64>, true, true>("x3d_128x128x32_w64x64"));
-    out.push_back(make_x3<X3S, Shape<64, 64, 32, 32, 32>, true, true>("x3_64x64x32_w32x32"));
+    out.push_back(make_x3<X3D, Shape<64, 64, 32, 32, 32>, true, true>("x3_64x64x32_w32x32"));
     out.push_back(make_x3<X3W, WShape<64, 64, 64, 4>, true>("x3w_64x64x64_k4"));
     out.push_back(make_x3<X3W, WShape<32, 32, 64, 4>, true>("x3w_32x32x64_k4"));
     // register tiles: four waves take 64-k chunks in turn
