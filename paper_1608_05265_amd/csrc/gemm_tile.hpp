@@ -1090,8 +1090,8 @@ struct X3PTile {
 };
 
 // The split form of the small tile: each K block holds KW steps of 16 k,
-// one per wave, split while staged; a wave adds its six part products
-// smallest first into one accumulator, as the large split-form tiles do.
+// one per wave, split while staged; a wave adds its leading part products into
+// one accumulator and the five small ones, smallest first, into another.
 template <class SH, bool TA, bool TB>
 struct X3WTile {
     using SA = StageX3<SH::BM, SH::BK, SH::NT, TA>;
@@ -1121,13 +1121,13 @@ struct X3WTile {
         __bf16 *lds = reinterpret_cast<__bf16 *>(smem);
         const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
         const int half = lane >> 5, l32 = lane & 31;
-        floatx16 acc[RM][RN];
+        floatx16 acc[RM][RN], lo[RM][RN];
 #pragma unroll
         for (int i = 0; i < RM; ++i)
 #pragma unroll
             for (int j = 0; j < RN; ++j)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+                for (int e = 0; e < 16; ++e) acc[i][j][e] = lo[i][j][e] = 0.0f;
         const KBlocks<SH::BK> kb(g.k);
         const int64_t ktiles = kb.count;
         SA sa;
@@ -1167,13 +1167,14 @@ struct X3WTile {
                 for (int i = 0; i < RM; ++i)
 #pragma unroll
                     for (int j = 0; j < RN; ++j) {
-                        floatx16 &c = acc[i][j];
+                        floatx16 &c = lo[i][j];
                         c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][0], b[j][2], c, 0, 0, 0);
                         c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][1], b[j][1], c, 0, 0, 0);
                         c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][2], b[j][0], c, 0, 0, 0);
                         c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][0], b[j][1], c, 0, 0, 0);
                         c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][1], b[j][0], c, 0, 0, 0);
-                        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][0], b[j][0], c, 0, 0, 0);
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][0], b[j][0],
+                                                                            acc[i][j], 0, 0, 0);
                     }
             }
             if (more) {
@@ -1182,6 +1183,10 @@ struct X3WTile {
             }
             __syncthreads();
         }
+#pragma unroll
+        for (int i = 0; i < RM; ++i)
+#pragma unroll
+            for (int j = 0; j < RN; ++j) acc[i][j] += lo[i][j];
         wave_sum<KW, RM, RN>(acc, reinterpret_cast<float *>(smem), wave, lane);
         if (wave == 0) epilogue<RM, RN>(g, acc, m0, n0, lane);
     }
