@@ -850,10 +850,11 @@ struct X3Tile {
 // block kt from LDS, the global loads of block kt+1 are in flight, and once a
 // fraction Q0_NUM/Q0_DEN of the block's MFMA instructions are issued the
 // split and LDS store of block kt+1 are interleaved between the remaining
-// ones.  One workgroup barrier per K block.
+// ones.  One workgroup barrier per K block.  HILO: the leading products in one
+// accumulator and the five small ones in another: a third of the error.
 // ---------------------------------------------------------------------------
 template <class SH, bool TA, bool TB, int Q0_NUM = 1, int Q0_DEN = 3, bool FENCED = false,
-          bool PF2 = false>
+          bool PF2 = false, bool HILO = false>
 struct X3PTile {
     using SA = StageX3<SH::BM, SH::BK, SH::NT, TA>;
     using SB = StageX3<SH::BN, SH::BK, SH::NT, !TB>;
@@ -864,6 +865,7 @@ struct X3PTile {
     static constexpr int NT = SH::NT;
     static constexpr int RM = SH::RM, RN = SH::RN;
     static constexpr int NMFMA = RM * RN * 6;
+    static constexpr int LM = HILO ? RM : 1, LN = HILO ? RN : 1;
     static constexpr int NELEM = SA::KS * (SA::UNITS + SB::UNITS);
     // first MFMA slot that carries split/store work for the next block
     static constexpr int Q0 = NMFMA * Q0_NUM / Q0_DEN;
@@ -895,7 +897,8 @@ struct X3PTile {
     }
 
     template <bool STORE>
-    __device__ __forceinline__ static void body(floatx16 (&acc)[RM][RN], const __bf16 *cur,
+    __device__ __forceinline__ static void body(floatx16 (&acc)[RM][RN], floatx16 (&lo)[LM][LN],
+                                                const __bf16 *cur,
                                                 __bf16 *nxt, const SA &sa, const SB &sb,
                                                 int tid, int wm, int wn, int half, int l32)
     {
@@ -925,8 +928,9 @@ struct X3PTile {
                     for (int i = 0; i < RM; ++i) {
                         const int sa_i = pr == 0 ? 0 : pr == 1 ? 1 : pr == 2 ? 2 : pr == 3 ? 0 : pr == 4 ? 1 : 0;
                         const int sb_j = pr == 0 ? 2 : pr == 1 ? 1 : pr == 2 ? 0 : pr == 3 ? 1 : pr == 4 ? 0 : 0;
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                            a[i][sa_i], b[j & 1][sb_j], acc[i][j], 0, 0, 0);
+                        floatx16 &c = HILO && pr < 5 ? lo[HILO ? i : 0][HILO ? j : 0] : acc[i][j];
+                        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][sa_i], b[j & 1][sb_j], c,
+                                                                    0, 0, 0);
                         __builtin_amdgcn_sched_barrier(0);
                         if (i == 0 && pr == 0 && j + 1 < RN) {
 #pragma unroll
@@ -958,8 +962,8 @@ struct X3PTile {
                 for (int i = 0; i < RM; ++i) {
                     const int sa_i = pr == 0 ? 0 : pr == 1 ? 1 : pr == 2 ? 2 : pr == 3 ? 0 : pr == 4 ? 1 : 0;
                     const int sb_j = pr == 0 ? 2 : pr == 1 ? 1 : pr == 2 ? 0 : pr == 3 ? 1 : pr == 4 ? 0 : 0;
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][sa_i], b[j & 1][sb_j],
-                                                                         acc[i][j], 0, 0, 0);
+                    floatx16 &c = HILO && pr < 5 ? lo[HILO ? i : 0][HILO ? j : 0] : acc[i][j];
+                    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][sa_i], b[j & 1][sb_j], c, 0, 0, 0);
                     if (i == 0 && pr == 0 && j + 1 < RN) {
 #pragma unroll
                         for (int t = 0; t < 3; ++t)
@@ -1017,13 +1021,21 @@ struct X3PTile {
         const int wm = wave % SH::NWM, wn = wave / SH::NWM;
         const int half = lane >> 5, l32 = lane & 31;
 
-        floatx16 acc[RM][RN];
+        floatx16 acc[RM][RN], lo[LM][LN];
 #pragma unroll
         for (int i = 0; i < RM; ++i)
 #pragma unroll
             for (int j = 0; j < RN; ++j)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+                for (int e = 0; e < 16; ++e) acc[i][j][e] = lo[HILO ? i : 0][HILO ? j : 0][e] = 0.0f;
+        const auto join = [&] {
+            if constexpr (HILO) {
+#pragma unroll
+                for (int i = 0; i < RM; ++i)
+#pragma unroll
+                    for (int j = 0; j < RN; ++j) acc[i][j] += lo[i][j];
+            }
+        };
 
         const KBlocks<SH::BK> kb(g.k);
         const int64_t ktiles = kb.count;
@@ -1055,13 +1067,14 @@ struct X3PTile {
                 }
                 // a store whose block does not exist rewrites an idle stage
                 // that nothing reads again
-                body<true>(acc, cur, nxt, sa, sb, tid, wm, wn, half, l32);
+                body<true>(acc, lo, cur, nxt, sa, sb, tid, wm, wn, half, l32);
                 if (kt + 2 < ktiles) {
                     sa = sa2;
                     sb = sb2;
                 }
                 __syncthreads();
             }
+            join();
             finish<SPLIT, RM, RN>(g, acc, m0 + wm * SH::WM, n0 + wn * SH::WN, tid, NT);
             return;
         }
@@ -1082,9 +1095,10 @@ struct X3PTile {
             // On the last block the store rewrites the idle buffer with the
             // block already consumed; nothing reads it afterwards.  One body
             // for every iteration keeps the accumulators in place.
-            body<true>(acc, cur, nxt, sa, sb, tid, wm, wn, half, l32);
+            body<true>(acc, lo, cur, nxt, sa, sb, tid, wm, wn, half, l32);
             __syncthreads();
         }
+        join();
         finish<SPLIT, RM, RN>(g, acc, m0 + wm * SH::WM, n0 + wn * SH::WN, tid, NT);
     }
 };

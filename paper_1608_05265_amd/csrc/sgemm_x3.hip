@@ -18,7 +18,10 @@ using X3D = X3Tile<SH, TA, TB, true>;
 // pipelined: split/store of the next block starts after 1/3 of the MFMAs
 template <class SH, bool TA, bool TB>
 using X3P13 = X3PTile<SH, TA, TB, 1, 3>;
-// the same with the order pinned by fences instead of group barriers
+// the same with the leading products in an accumulator of their own
+template <class SH, bool TA, bool TB>
+using X3H13 = X3PTile<SH, TA, TB, 1, 3, false, false, true>;
+// X3P13 with the order pinned by fences instead of group barriers
 template <class SH, bool TA, bool TB>
 using X3F13 = X3PTile<SH, TA, TB, 1, 3, true>;
 // pipelined with the global loads two K blocks ahead (two register sets)
@@ -75,7 +78,9 @@ void register_x3(std::vector<ConfigEntry> &out)
     out.push_back(make_x3<X3F13, Shape<256, 256, 16, 128, 64>, false>("x3f_256x256x16_w128x64"));
     out.push_back(make_x3<X3F13, Shape<256, 256, 16, 64, 128>, false>("x3f_256x256x16_w64x128"));
     out.push_back(make_x3<X3F13, Shape<256, 256, 16, 128, 128>, false>("x3f_256x256x16_w128x128"));
-    out.push_back(make_x3<X3P13, Shape<128, 128, 16, 64, 64>, true, true>("x3p_128x128x16_w64x64"));
+    // two sums fit the registers of two waves per SIMD, which the batched
+    // kernel, with the four transposes' loops in it, needs for one
+    out.push_back(make_x3<X3H13, Shape<128, 128, 16, 64, 64, 2>, true, true, X3P13>("x3p_128x128x16_w64x64"));
     out.push_back(make_x3<X3Q13, Shape<128, 128, 16, 64, 64>, true, true>("x3q_128x128x16_w64x64"));
     out.push_back(make_x3<X3S, Shape<128, 128, 32, 64, 64>, true>("x3_128x128x32_w64x64"));
     out.push_back(make_x3<X3D, Shape<128, 128, 32, 64, 64>, true, true>("x3d_128x128x32_w64x64"));
