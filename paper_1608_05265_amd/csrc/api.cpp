@@ -296,13 +296,14 @@ int batch_model_config(const misgemm_problem *problems, int64_t count, int mode,
     return best;
 }
 
-// The nearest tuned entry, else the model's choice.
+// The nearest tuned entry (*tuned), else the model's choice.
 int select_config(int mode, int ta, int tb, int64_t m, int64_t n, int64_t k, int cus,
-                  bool allow_packed, bool allow_split, int *group_m, int *splits)
+                  bool allow_packed, bool allow_split, int *group_m, int *splits, bool *tuned)
 {
     *group_m = GROUP_M_DEFAULT;
     *splits = 0;
     const int c = tuned_config(mode, ta, tb, m, n, k, allow_packed, group_m, splits);
+    *tuned = c >= 0;
     if (c >= 0) return c;
     *group_m = GROUP_M_DEFAULT;
     return model_config(mode, m, n, k, cus, allow_packed, allow_split, splits);
@@ -503,7 +504,8 @@ int effective_splits(int64_t k, int bk, int req)
     return (int)((kt + per - 1) / per);
 }
 
-// splits_req: 0 = automatic (tuning table, then auto_splits), >= 1 = forced.
+// splits_req: 0 = automatic (the tuning table's or the model's; auto_splits for
+// an explicit configuration and a table's 0), >= 1 = forced.
 int run_sgemm(char transa, char transb, int64_t m, int64_t n, int64_t k, float alpha,
               const float *A, int64_t lda, const float *B, int64_t ldb, float beta, float *C,
               int64_t ldc, int mode, int config_id, int group_m, void *stream,
@@ -533,8 +535,10 @@ int run_sgemm(char transa, char transb, int64_t m, int64_t n, int64_t k, float a
     int cfg = config_id;
     int splits = splits_req;
     int tuned_splits = 0;
+    bool tuned = true;  // the configuration is the caller's or the table's
     if (cfg < 0) cfg = select_config(mode, ta, tb, m, n, k, dev->cus, packable,
-                                     policy == WS_LIBRARY && splits_req == 0, &gm, &tuned_splits);
+                                     policy == WS_LIBRARY && splits_req == 0, &gm, &tuned_splits,
+                                     &tuned);
     if (cfg < 0) return MISGEMM_E_BAD_CONFIG;
     if (splits == 0) splits = tuned_splits;
     void *ws = nullptr;
@@ -584,8 +588,14 @@ int run_sgemm(char transa, char transb, int64_t m, int64_t n, int64_t k, float a
         }
         if (forced) return wrc != 0 ? wrc : MISGEMM_E_CAPTURING;
         if (wrc != 0 && wrc != MISGEMM_E_CAPTURING) return wrc;
+        if (!tuned) {
+            // the model's tile for a split leaves CUs idle without it: its
+            // choice for whole K (512x512x16384 would run on 64 of 256)
+            int whole = 1;
+            cfg = model_config(mode, m, n, k, dev->cus, false, false, &whole);
+        }
     }
-    return (int)e.launch[ta][tb](g, gm, s);
+    return (int)table[cfg].launch[ta][tb](g, gm, s);
 }
 
 }  // namespace
@@ -1029,7 +1039,8 @@ int misgemm_select_config(char transa, char transb, int64_t m, int64_t n, int64_
     int cus = 256;
     if (current_device(&dev) == 0) cus = dev->cus;
     int gm = 0, splits = 0;
-    return select_config(mode, ta, tb, m, n, k, cus, false, true, &gm, &splits);
+    bool tuned = false;
+    return select_config(mode, ta, tb, m, n, k, cus, false, true, &gm, &splits, &tuned);
 }
 
 int misgemm_load_tuning(const char *path)
