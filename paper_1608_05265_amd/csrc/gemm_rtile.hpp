@@ -149,6 +149,10 @@ template <class SH, bool TA, bool TB, class MATH>
 struct RTileBase {
     static constexpr int KW = SH::KW, RM = SH::RM, RN = SH::RN, NT = SH::NT, KPL = SH::KPL;
     static constexpr int LDS_BYTES = (KW > 1 ? (KW - 1) : 1) * RM * RN * 4 * 64 * 4;
+    // Thin problems put many tiles on a CU, whose waves hide each other's
+    // loads: the second partial sum must not cost one (97648x6x64 TT, three
+    // waves for four: 15.9 us for 12.8).
+    static constexpr int WAVES = MATH::waves(SH::BM, KPL, TA, !TB);
 
     template <bool SPLIT = false>
     __device__ __forceinline__ static void run(const GemmArgs &g, int64_t m0, int64_t n0,
@@ -236,6 +240,13 @@ struct RTileBase {
 // 1024 were rounded 1.4 times as far off (5.75e-7 for 4.12e-7).
 struct RMathF32 {
     static constexpr int CHAINS = 2;
+    // as many waves as one sum took; a, b: whether op(A), op(B) is stored
+    // k-contiguous, which takes fewer registers for its loads
+    static constexpr int waves(int bm, int kpl, bool a, bool b)
+    {
+        if (kpl == 8) return 1;
+        return bm == 16 ? 3 + a + b : a || b ? 2 : 1;
+    }
     template <int RM, int RN, int KPL>
     __device__ __forceinline__ static void step(const float (&a)[RM][KPL],
                                                 const float (&b)[RN][KPL],
@@ -255,6 +266,11 @@ struct RMathF32 {
 // Two chains here too: the leading products and the five small ones.
 struct RMathX3 {
     static constexpr int CHAINS = 2;
+    static constexpr int waves(int bm, int kpl, bool a, bool b)
+    {
+        if (kpl == 8) return a && b ? 7 : b ? 6 : a ? 5 : 4;
+        return bm == 16 ? 2 + a + b : a && b ? 2 : 1;
+    }
     template <int RM, int RN, int KPL>
     __device__ __forceinline__ static void step(const float (&a)[RM][KPL],
                                                 const float (&b)[RN][KPL],

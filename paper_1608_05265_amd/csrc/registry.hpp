@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
 #include <vector>
 
 #include "../../include/misgemm.h"
@@ -64,8 +65,15 @@ inline bool has_batch(const ConfigEntry &e) { return e.batch != nullptr || e.pac
 // Default number of tile-rows walked together (see tile_coords).
 constexpr int GROUP_M_DEFAULT = 8;
 
+// Waves per SIMD that a single call's kernel must leave registers for: the
+// tile's own number, where it has one (its transposes differ), else its shape's.
+template <class TILE, class SH, class = void>
+struct Waves { static constexpr int value = SH::OCC; };
 template <class TILE, class SH>
-__global__ __launch_bounds__(SH::NT, SH::OCC) void sgemm_kernel(GemmArgs g, int64_t tiles_m,
+struct Waves<TILE, SH, std::void_t<decltype(TILE::WAVES)>> { static constexpr int value = TILE::WAVES; };
+
+template <class TILE, class SH>
+__global__ __launch_bounds__(SH::NT, (Waves<TILE, SH>::value)) void sgemm_kernel(GemmArgs g, int64_t tiles_m,
                                                           int64_t tiles_n, int group_m)
 {
     __shared__ __attribute__((aligned(16))) char smem[TILE::LDS_BYTES];
