@@ -303,13 +303,15 @@ int misgemm_sgetrf(int64_t n, float *A, int64_t lda, int64_t *ipiv, int *info, i
  * of a panel of several workgroups.  wait_polls: polls the first workgroup
  * waits for the others (negative: none, it factors the panel alone, in
  * memory); word_polls: polls the others wait for its word (0: none, they call
- * the panel off).  misgemm_sgetrf_waiting takes the second bound of
- * misgemm_sgetrf.  Arguments and errors otherwise as there.
+ * the panel off); max_groups: workgroups a panel may take (up to the library's
+ * own bound of 64, i.e. 65536 rows), above which it is 8 columns factored in
+ * memory.  misgemm_sgetrf_waiting takes the other bounds of misgemm_sgetrf.
+ * Arguments and errors otherwise as there.
  */
 int misgemm_sgetrf_waiting(int64_t n, float *A, int64_t lda, int64_t *ipiv, int *info, int mode,
                            int wait_polls, void *stream);
 int misgemm_sgetrf_limited(int64_t n, float *A, int64_t lda, int64_t *ipiv, int *info, int mode,
-                           int wait_polls, int word_polls, void *stream);
+                           int wait_polls, int word_polls, int max_groups, void *stream);
 
 /*
  * Solve A X = B with the factors of misgemm_sgetrf: B (n x nrhs, device,

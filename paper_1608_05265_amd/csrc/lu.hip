@@ -333,6 +333,7 @@ struct Lu {
     // bounds of a panel's start: the first workgroup's wait for the others and
     // the others' for its word
     int wait_polls, word_polls;
+    int max_groups;  // workgroups of a panel; taller ones are factored in memory
 };
 
 int check(hipError_t e) { return e == hipSuccess ? 0 : (int)e; }
@@ -435,13 +436,16 @@ int64_t panel_groups(int64_t m)
 }
 
 // Columns of a panel of m rows.
-int64_t panel_width(int64_t m) { return panel_groups(m) <= PANEL_GROUPS ? PANEL : TALL_PANEL; }
+int64_t panel_width(const Lu &c, int64_t m)
+{
+    return panel_groups(m) <= c.max_groups ? PANEL : TALL_PANEL;
+}
 
 // Factor the panel at P (m x w, top-left element A(j0, j0)).
 int panel(const Lu &c, float *P, int64_t m, int w, int64_t j0)
 {
     const int64_t groups = panel_groups(m);
-    if (groups > PANEL_GROUPS) {
+    if (groups > c.max_groups) {
         hipLaunchKernelGGL(lu_panel_tall_kernel, dim3(1), dim3(TALL_THREADS), 0, c.s, P, c.lda, m,
                            w, c.ipiv, j0, c.info);
         return check(hipGetLastError());
@@ -475,7 +479,7 @@ int getrf(const Lu &c, int64_t j0, int64_t w)
 {
     const int64_t m = c.n - j0;
     float *P = c.A + j0 + j0 * c.lda;
-    const int64_t pw = panel_width(m);
+    const int64_t pw = panel_width(c, m);
     int rc;
     if (w <= pw) {
         if ((rc = panel(c, P, m, (int)w, j0))) return rc;
@@ -498,7 +502,7 @@ bool lu_mode_ok(int mode) { return mode == MISGEMM_FP32 || mode == MISGEMM_BF16X
 extern "C" {
 
 int misgemm_sgetrf_limited(int64_t n, float *A, int64_t lda, int64_t *ipiv, int *info, int mode,
-                           int wait_polls, int word_polls, void *stream)
+                           int wait_polls, int word_polls, int max_groups, void *stream)
 {
     if (n < 0) return -1;
     if (n > 0 && A == nullptr) return -2;
@@ -512,20 +516,23 @@ int misgemm_sgetrf_limited(int64_t n, float *A, int64_t lda, int64_t *ipiv, int 
                        info);
     int rc = check(hipGetLastError());
     if (rc != 0 || n == 0) return rc;
-    const Lu c{A, lda, n, ipiv, info, mode, s, wait_polls, word_polls};
+    const Lu c{A, lda, n, ipiv, info, mode, s, wait_polls, word_polls,
+               max_groups < PANEL_GROUPS ? max_groups : PANEL_GROUPS};
     return getrf(c, 0, n);
 }
 
 int misgemm_sgetrf_waiting(int64_t n, float *A, int64_t lda, int64_t *ipiv, int *info, int mode,
                            int wait_polls, void *stream)
 {
-    return misgemm_sgetrf_limited(n, A, lda, ipiv, info, mode, wait_polls, PANEL_WORD_WAIT, stream);
+    return misgemm_sgetrf_limited(n, A, lda, ipiv, info, mode, wait_polls, PANEL_WORD_WAIT,
+                                  PANEL_GROUPS, stream);
 }
 
 int misgemm_sgetrf(int64_t n, float *A, int64_t lda, int64_t *ipiv, int *info, int mode,
                    void *stream)
 {
-    return misgemm_sgetrf_limited(n, A, lda, ipiv, info, mode, PANEL_WAIT, PANEL_WORD_WAIT, stream);
+    return misgemm_sgetrf_limited(n, A, lda, ipiv, info, mode, PANEL_WAIT, PANEL_WORD_WAIT,
+                                  PANEL_GROUPS, stream);
 }
 
 int misgemm_sgetrs(int64_t n, int64_t nrhs, const float *A, int64_t lda, const int64_t *ipiv,
@@ -541,7 +548,7 @@ int misgemm_sgetrs(int64_t n, int64_t nrhs, const float *A, int64_t lda, const i
     if (!lu_mode_ok(mode)) return -8;
     if (n == 0 || nrhs == 0) return 0;
     const Lu c{const_cast<float *>(A), lda, n, const_cast<int64_t *>(ipiv), nullptr, mode,
-               (hipStream_t)stream, 0, 0};
+               (hipStream_t)stream, 0, 0, 0};
     const bool few = nrhs <= TRSV_MAX_RHS;
     int rc = 0;
     if (few && n <= LASWP_LDS_ROWS) {

@@ -12,20 +12,23 @@ pytestmark = pytest.mark.gpu
 EPS32 = 2.0 ** -24
 PANEL_WAIT = 1 << 16  # the library's own bounds
 WORD_WAIT = 1 << 18
+GROUPS = 64
 
 
 def _limited():
     import paper_1608_05265_amd as mg
     fn = mg._load().misgemm_sgetrf_limited
     fn.argtypes = [ctypes.c_int64, ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p,
-                   ctypes.c_void_p, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_void_p]
+                   ctypes.c_void_p, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int,
+                   ctypes.c_void_p]
     return fn
 
 
 class Factors:
     """The factorization of a (queued on `stream`, not waited for)."""
 
-    def __init__(self, a, stream=None, wait_polls=PANEL_WAIT, word_polls=WORD_WAIT, sync=True):
+    def __init__(self, a, stream=None, wait_polls=PANEL_WAIT, word_polls=WORD_WAIT, groups=GROUPS,
+                 sync=True):
         import torch
         n = a.shape[0]
         self.A = torch.from_numpy(np.ascontiguousarray(a.T)).to("cuda:0")
@@ -36,7 +39,7 @@ class Factors:
         if sync:
             torch.cuda.synchronize()
         rc = _limited()(n, self.A.data_ptr(), n, self.piv.data_ptr(), self.inf.data_ptr(), 0,
-                        wait_polls, word_polls, s.cuda_stream)
+                        wait_polls, word_polls, groups, s.cuda_stream)
         assert rc == 0
 
     def get(self):
@@ -135,11 +138,14 @@ def _panel(a):
     return a, piv
 
 
-@pytest.mark.parametrize("n", [5, 50, 64, 200, 600, 1100, 2600])
+@pytest.mark.parametrize("n", [5, 50, 64, 200, 512, 513, 1024, 1025, 2600, 6144, 6145, 12289, 16385])
 def test_first_panel_bit_for_bit(n):
-    """One workgroup with one and two rows per thread, several workgroups,
-    whole and partial blocks, against the same sums in numpy."""
-    a = np.random.default_rng(68).uniform(-1, 1, (n, n)).astype(np.float32)
+    """Against the same sums in numpy: whole and partial blocks, one workgroup
+    of one (to 512 rows) and two rows per thread (to 1024), up to 12 workgroups
+    of one row per thread (to 6144), two rows per thread again (from 6145), more
+    than the 12 whose messages come in one round trip (from 12289), all XCDs
+    (from 16385)."""
+    a = np.random.default_rng(68).random((n, n), np.float32) - np.float32(0.5)
     w = min(n, 64)
     want, piv = _panel(a[:, :w])
     lu, ipiv, info = Factors(a).get()
@@ -244,3 +250,25 @@ def test_a_column_of_nan_stays_out_of_the_panel():
     assert info == info2 == 1 and np.array_equal(ipiv, ipiv2)
     keep = [c for c in range(64) if c not in (0, 5, 18)]
     assert np.array_equal(lu[:, keep], lu2[:, keep])
+
+
+@pytest.mark.parametrize("groups", [0, 1, 3])
+def test_panels_taller_than_the_workgroups_hold(groups):
+    """With fewer workgroups allowed to a panel, one that would need more is 8
+    columns factored in memory; the factorization goes over to 64 columns in
+    registers where the rest fits (at 1024 and 1536 rows; never with none)."""
+    n = 3000
+    a, want = _dominant(n, 75)
+    _check(Factors(a, groups=groups).get(), want, n)
+    a = np.random.default_rng(76).uniform(-1, 1, (n, n)).astype(np.float32)
+    lu, ipiv, info = Factors(a, groups=groups).get()
+    lu = lu.astype(np.float64)
+    assert info == 0 and np.all(ipiv >= np.arange(n)) and np.all(ipiv < n)
+    L, U = np.tril(lu, -1) + np.eye(n), np.triu(lu)
+    assert np.max(np.abs(L)) <= 1.0 + 1e-6
+    pa = a.astype(np.float64)
+    for j, p in enumerate(ipiv):
+        pa[[j, p]] = pa[[p, j]]
+    # entry by entry the backward-error bound of LU, about n eps, as the other
+    # sizes' tests take it
+    assert np.all(np.abs(pa - L @ U) <= 4 * n * EPS32 * (np.abs(L) @ np.abs(U)))
