@@ -70,6 +70,20 @@ def default_keys():
 LD_PAD = 16
 
 
+def kernels(mode):
+    """The configurations of a form, one per kernel: FP32 ones that differ in
+    nothing but the prefix of their name are the same kernel."""
+    import paper_1608_05265_amd as mg
+    out, seen = [], set()
+    for cfg in mg.configs(mode):
+        key = tuple(v for k, v in cfg.items() if k not in ("id", "name"))
+        if mode == mg.FP32 and key in seen:
+            continue
+        seen.add(key)
+        out.append(cfg)
+    return out
+
+
 def tune_gemm(keys, reps=5, warmup=2, log=print):
     import torch
     import paper_1608_05265_amd as mg
@@ -96,7 +110,7 @@ def tune_gemm(keys, reps=5, warmup=2, log=print):
         r, w = (reps * 4, warmup * 2) if small else (reps, warmup)
         timings = {}
         ids = {}
-        for cfg in mg.configs(mode):
+        for cfg in kernels(mode):
             ids[cfg["name"]] = cfg["id"]
             tiles = -(-m // cfg["bm"]) * -(-n // cfg["bn"])
             splits = [1] + (SPLITS if cfg["splitk"] and tiles < 2 * cus else [])
@@ -148,7 +162,7 @@ def tune_batch(problems, reps=5, warmup=2, log=print):
     out = {}
     for mode in (0, 1):
         timings = {}
-        for cfg in mg.configs(mode):
+        for cfg in kernels(mode):
             try:
                 plan = mg.Batch(descs, mode=mode, config_id=cfg["id"])
             except mg.MisgemmError:
@@ -166,8 +180,8 @@ def tune_batch(problems, reps=5, warmup=2, log=print):
         rules = {}
         side = torch.cuda.Stream()
         main = torch.cuda.current_stream()
-        bigs = [c for c in mg.configs(mode) if c["bm"] >= 128 and c["bn"] >= 128]
-        smalls = [c for c in mg.configs(mode) if c["bm"] <= 64 and c["bn"] <= 64]
+        bigs = [c for c in kernels(mode) if c["bm"] >= 128 and c["bn"] >= 128]
+        smalls = [c for c in kernels(mode) if c["bm"] <= 64 and c["bn"] <= 64]
         for thr in (192, 256, 384):
             ib = [i for i, p in enumerate(problems) if p.m >= thr and p.n >= thr]
             isml = [i for i, p in enumerate(problems) if not (p.m >= thr and p.n >= thr)]

@@ -2,6 +2,9 @@
 one of its mode that runs without a workspace, and the choice follows what
 the model is made of -- whole cards of tiles take large tiles, few tiles small
 ones, and a ragged size the same as its neighbours."""
+import os
+import re
+
 import numpy as np
 import pytest
 
@@ -48,3 +51,25 @@ def test_choice_fits_a_launch(mode):
         c = cfgs[mg.select_config("N", "N", m, n, k, mode)]
         tiles = -(-m // c["bm"]) * -(-n // c["bn"])
         assert tiles * c["threads"] < 1 << 32, (m, n, k, c["name"])
+
+
+def test_every_row_names_a_configuration():
+    """A row whose configuration is gone would be left out without a word."""
+    src = open(os.path.join(os.path.dirname(mg.__file__), "csrc", "api.cpp")).read()
+    for mode, table in ((0, "FP32_ROWS"), (1, "X3_ROWS")):
+        body = re.search(r"const CostRow %s\[\] = \{(.*?)\n\};" % table, src, re.S).group(1)
+        rows = re.findall(r'\{"(\w+)"', body)
+        names = {c["name"] for c in mg.configs(mode)}
+        assert len(rows) >= 10 and set(rows) <= names, set(rows) - names
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+def test_tuner_times_each_kernel_once(mode):
+    from paper_1608_05265_amd import autotune
+    shape = lambda c: tuple(v for k, v in c.items() if k not in ("id", "name"))
+    kept, every = autotune.kernels(mode), mg.configs(mode)
+    assert {shape(c) for c in kept} == {shape(c) for c in every}
+    if mode == 0:
+        assert len(kept) == len({shape(c) for c in every}) < len(every)
+    else:
+        assert kept == every
