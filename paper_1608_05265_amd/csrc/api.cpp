@@ -136,15 +136,25 @@ int tuned_config(int mode, int ta, int tb, int64_t m, int64_t n, int64_t k, bool
 // take w r / full together where the shape fills the CU, and at least
 // w / alone each (`resident` at a time) where it does not; starting the
 // launch takes `start` us and reading and writing C `store` us per 100 x 100
-// of it.  The five numbers of a row were fitted to the times of every
-// configuration on 95 shapes (64 to 6144 a side, rank-k updates of up to
-// 16384 x 16384, K up to 16384, all transposes; three quarters of them
-// random), the 256-wide FP32 rows and `top` to 8192^3 as well.  Over these the choice is 1.4 % (FP32) and 1.5 % (split form,
-// with a caller's workspace too) slower than the fastest configuration of
-// each, at worst 20 %.  The largest tile that gives every
-// CU one, the nearest of the tuned squares before that, and two workgroups
-// per CU by splits chose, in us: 1536x1536x8192 515 for 385, 3000x3000x300
-// 93 for 57, 10144x8795x64 249 for 207, 1511x777x1003 44 for 37.
+// of it.  The five numbers of a row are a least-squares fit, in the logarithm,
+// to the times of every configuration of that row's form on 95 shapes (64 to
+// 6144 a side, rank-k updates of up to 16384 x 16384, K up to 16384, all
+// transposes; three quarters of them random), the 256-wide FP32 rows and `top`
+// to 8192^3 as well.  Over these the choice is 1.4 % (FP32) and 1.5 % (split
+// form, with a caller's workspace too) slower than the fastest configuration
+// of each, at worst 20 %.  The rows of the staged split-form tiles are from
+// before their K loop was dealt out, which made them 8 to 17 % faster: a fit
+// to the new times chose 1.3 % from the fastest, and they were left; so their
+// times, and 4096^3 (568 us by the model, 634 measured), are no predictions,
+// only their order is used.  The largest tile that gives every CU one, the
+// nearest of the tuned squares before that, and two workgroups per CU by
+// splits chose, in us: 1536x1536x8192 515 for 385, 3000x3000x300 93 for 57,
+// 10144x8795x64 249 for 207, 1511x777x1003 44 for 37.
+//
+// The choice also sets how many partial sums an output has (one over K in the
+// staged tiles, two or more in the others), and with it the error, which is
+// no part of the model: against the choices before, FP32 0.87 times the rms
+// error on average over 60 drawn shapes (0.5 to 1.8), split form 0.51.
 // ---------------------------------------------------------------------------
 struct CostRow {
     const char *name;
@@ -432,7 +442,6 @@ hipError_t launch_packed_path(const ConfigEntry &cfg, int ta, int tb, const Gemm
     p.kblocks = pack_kblocks(g.k);
     return cfg.packed(p, group_m, s);
 }
-
 
 int validate(char transa, char transb, int64_t m, int64_t n, int64_t k, float alpha,
              const float *A, int64_t lda, const float *B, int64_t ldb, float *C, int64_t ldc,

@@ -129,7 +129,7 @@ struct DArgs {
 // reads one K step ahead of their MFMAs, across the barrier too, which
 // stands before the last K step of a block.  With two register sets, but
 // stores, barrier and reads in lumps at the ends of a block, 2048^3 took
-// 259-271 us; with one set 287-316 us; now 241 us (71 TFLOP/s).
+// 259-271 us; with one set 287-316 us; now 248-252 us (69 TFLOP/s).
 // ---------------------------------------------------------------------------
 template <int BM_, int BN_, int BK_, int WM_, int WN_, int KW_, int OCC_>
 struct DShape {

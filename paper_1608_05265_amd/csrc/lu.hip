@@ -6,7 +6,7 @@
 // the rank-k trailing update), factor A22.  Almost all flops land in sgemm
 // calls of decreasing size.  The leaves are panels of 64 columns that one
 // launch factors with their rows in the registers of several workgroups
-// (lu.panel.hpp); panels of more rows than those hold are factored in memory
+// (lu_panel.hpp); panels of more rows than those hold are factored in memory
 // by one workgroup, 8 columns at a time.  Each panel's row interchanges are
 // applied to every other column of the matrix right after it, which gives
 // the same result as swapping at each level of the recursion (a column
@@ -21,7 +21,7 @@
 #include <stdint.h>
 
 #include "../../include/misgemm.h"
-#include "lu.panel.hpp"
+#include "lu_panel.hpp"
 
 namespace {
 
@@ -423,7 +423,8 @@ int trsm(const Lu &c, bool upper, const float *T, int64_t ldt, float *B, int64_t
 // 0.5 us less of a column's own work, more workgroups cost more to exchange:
 // 64 columns of 1024 rows take 106 us as one workgroup of two rows per thread
 // and 123 as two of one; 2048 rows 158 and 127 us, 4608 rows 171 and 146, 8192
-// rows 165 and 194.
+// rows 165 and 194 (before the block's products were summed apart, which adds
+// 1 us to each).
 int panel_rpt(int64_t m)
 {
     if (m <= 2 * PANEL_THREADS) return m <= PANEL_THREADS ? 1 : 2;
