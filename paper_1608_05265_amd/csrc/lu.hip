@@ -6,7 +6,7 @@
 // the rank-k trailing update), factor A22.  Almost all flops land in sgemm
 // calls of decreasing size.  The leaves are panels of 64 columns that one
 // launch factors with their rows in the registers of several workgroups
-// (lu_panel.hpp); panels of more rows than those hold are factored in memory
+// (lu.panel.hpp); panels of more rows than those hold are factored in memory
 // by one workgroup, 8 columns at a time.  Each panel's row interchanges are
 // applied to every other column of the matrix right after it, which gives
 // the same result as swapping at each level of the recursion (a column
@@ -21,7 +21,7 @@
 #include <stdint.h>
 
 #include "../../include/misgemm.h"
-#include "lu_panel.hpp"
+#include "lu.panel.hpp"
 
 namespace {
 
