@@ -62,7 +62,7 @@ typedef enum {
 #define MISGEMM_E_TUNING_FILE      1003 /* tuning file unreadable or malformed   */
 #define MISGEMM_E_BATCH            1004 /* bad batch (see bad_index)             */
 #define MISGEMM_E_NULL_PLAN        1005 /* plan pointer is NULL                  */
-#define MISGEMM_E_TOO_LARGE        1006 /* a size exceeds what the kernels index */
+#define MISGEMM_E_TOO_LARGE        1006 /* a size exceeds what the kernels index or a launch holds */
 #define MISGEMM_E_SCRATCH          1007 /* needs more than the static scratch    */
 
 /*
@@ -87,7 +87,7 @@ typedef enum {
  * second kernel adds the partials in split order and applies alpha/beta, so
  * results are reproducible bit for bit).
  * The scratch is allocated on first need and never while the stream is
- * being captured (the call then runs without it).  When a larger problem
+ * being captured (the call then runs the choice for whole K).  When a larger problem
  * outgrows it, the old buffer is freed after the work queued on the stream
  * has finished (the call synchronizes that stream once), unless a call
  * under graph capture used it: a graph may then still reference it, and it

@@ -235,7 +235,8 @@ def dgemm_host(transa: str, transb: str, m: int, n: int, k: int, alpha: float, A
 
 def sgetrf(n: int, A, lda: int, ipiv, info, mode=FP32, stream=None) -> None:
     """LU with partial pivoting of the n x n float32 device matrix A (in
-    place); ipiv an int64 device tensor of n, info an int32 device tensor."""
+    place); ipiv an int64 device tensor of n, info an int32 device tensor: 0, 1 +
+    the first column without a pivot, or -1 (no factorization: misgemm.h)."""
     rc = _load().misgemm_sgetrf(n, _ptr(A), lda, _ptr(ipiv), _ptr(info), _mode(mode),
                                 _stream(stream))
     _check(rc, "misgemm_sgetrf")
