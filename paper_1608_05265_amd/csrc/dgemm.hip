@@ -353,7 +353,8 @@ hipError_t launch_dgemm_fp64(int ta, int tb, int64_t m, int64_t n, int64_t k, do
     g.lda = lda; g.ldb = ldb; g.ldc = ldc;
     g.alpha = alpha; g.beta = beta;
     auto tiles = [&](int64_t edge) { return ((m + edge - 1) / edge) * ((n + edge - 1) / edge); };
-    if ((double)tiles(128) * 256 > UINT32_MAX) return hipErrorInvalidConfiguration;
+    if ((double)((m + 127) / 128) * (double)((n + 127) / 128) * 256 > UINT32_MAX)
+        return hipErrorInvalidConfiguration;
     if (tiles(64) * 256 > UINT32_MAX) {
         const int64_t half = (std::max(m, n) / 2 + 63) / 64 * 64;
         const bool rows = m > n;
